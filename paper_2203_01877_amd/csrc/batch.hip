@@ -3,10 +3,13 @@
 // work items from one device counter per stage, so a block that waits in a
 // look-back only ever waits on items handed out before its own.  The
 // sequence can be captured into a hipGraph and replayed, and an autotuner
-// picks the radix digit width and tile shape by timing the candidates.
+// picks the radix digit width and tile shape by timing the candidates.  A
+// batch whose fragments all have a small key domain runs without sorts
+// (flags_direct.hpp), the same launches under every configuration.
 #include <algorithm>
 #include <vector>
 
+#include "flags_direct.hpp"
 #include "fragment.hpp"
 
 namespace tqp {
@@ -314,9 +317,22 @@ struct HostTables {
     std::vector<int64_t> hist_prefix, pass_prefix, join_prefix;
 };
 
+// The table form of a batch: the fragments' key tables are cleared at every
+// run; descriptors and work items are uploaded once.
+struct DirectPlan {
+    size_t zero_bytes = 0;               // tables, at the start of the workspace
+    std::vector<FlagsDirect> frags;
+    std::vector<FlagsItem> dim_items, fact_items;
+    FlagsDirect* d_frags = nullptr;
+    FlagsItem* d_dim_items = nullptr;
+    FlagsItem* d_fact_items = nullptr;
+};
+
 struct tqp_batch {
     tqp_ctx* ctx = nullptr;
     int nf = 0;
+    bool direct = false;                 // every fragment takes the table form
+    DirectPlan dp;
     int cand_mask = (1 << NCAND) - 1;    // configurations planned in the workspace
     std::vector<tqp_flags_fragment> frags;
     std::vector<tqp_flags_out> outs;
@@ -458,9 +474,48 @@ size_t tables_bytes(int nf) {
            align256(sizeof(int64_t) * (nf + 1));
 }
 
+// Workspace of the table form: the tables (cleared at every run), the blocks'
+// sums, then the descriptors and work items.
+size_t plan_direct(tqp_batch* b, char* base) {
+    DirectPlan& dp = b->dp;
+    const int nf = b->nf;
+    dp.frags.assign(nf, FlagsDirect{});
+    dp.dim_items.clear();
+    dp.fact_items.clear();
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        char* p = base ? base + off : nullptr;
+        off += align256(bytes);
+        return p;
+    };
+    for (int f = 0; f < nf; ++f) {
+        const tqp_flags_fragment& fr = b->frags[f];
+        FlagsDirect& d = dp.frags[f];
+        flags_direct_fill(fr, b->outs[f], d);
+        d.bits = (uint32_t*)take((size_t)flags_direct_words(fr) * 4);
+        d.extra = (uint32_t*)take((size_t(1) << norm_key_bits(fr.key_bits)) * 4);
+        d.repeats = (uint32_t*)take(4);
+    }
+    dp.zero_bytes = off;
+    for (int f = 0; f < nf; ++f) {
+        const tqp_flags_fragment& fr = b->frags[f];
+        FlagsDirect& d = dp.frags[f];
+        for (int64_t r = 0; r < fr.n_dim; r += FLAGS_BATCH_DIM_ROWS)
+            dp.dim_items.push_back({f, 0, r, std::min(r + FLAGS_BATCH_DIM_ROWS, fr.n_dim)});
+        for (int64_t r = 0; r < fr.n_fact; r += FLAGS_BATCH_ROWS)
+            dp.fact_items.push_back({f, (int32_t)d.nslot++, r, std::min(r + FLAGS_BATCH_ROWS, fr.n_fact)});
+        d.part = (int64_t*)take((size_t)FLAGS_PART * d.nslot * 8);
+    }
+    dp.d_frags = (FlagsDirect*)take(sizeof(FlagsDirect) * nf);
+    dp.d_dim_items = (FlagsItem*)take(sizeof(FlagsItem) * dp.dim_items.size());
+    dp.d_fact_items = (FlagsItem*)take(sizeof(FlagsItem) * dp.fact_items.size());
+    return std::max<size_t>(256, off);
+}
+
 // Workspace: shared scratch, then each planned configuration's zero region,
 // then each planned configuration's descriptor tables.
 size_t plan_all(tqp_batch* b, char* base, std::vector<HostTables>* tables) {
+    if (b->direct) return plan_direct(b, base);
     const size_t scratch = scratch_bytes(b);
     size_t off = scratch;
     for (int c = 0; c < NCAND; ++c) {
@@ -489,22 +544,32 @@ size_t plan_all(tqp_batch* b, char* base, std::vector<HostTables>* tables) {
 // `stream` when given; the host copies stay alive in the batch).
 tqp_status upload_tables(tqp_batch* b, hipStream_t stream, bool sync) {
     const int S = 2 * b->nf, nf = b->nf;
-    for (int c = 0; c < NCAND; ++c) {
-        if (!(b->cand_mask & (1 << c))) continue;
-        CandPlan& cp = b->cand[c];
-        HostTables& ht = (*b->host)[c];
-        struct { void* d; const void* h; size_t n; } cps[5] = {
-            {cp.d_segs, ht.segs.data(), sizeof(BatchSeg) * S},
-            {cp.d_frags, ht.frags.data(), sizeof(BatchFrag) * nf},
-            {cp.d_hist_prefix, ht.hist_prefix.data(), sizeof(int64_t) * (S + 1)},
-            {cp.d_pass_prefix, ht.pass_prefix.data(), sizeof(int64_t) * 8 * (S + 1)},
-            {cp.d_join_prefix, ht.join_prefix.data(), sizeof(int64_t) * (nf + 1)}};
-        for (auto& x : cps) {
+    struct Copy { void* d; const void* h; size_t n; };
+    auto upload = [&](std::initializer_list<Copy> cps) -> tqp_status {
+        for (const Copy& x : cps) {
             if (!x.n) continue;
             hipError_t e = sync ? hipMemcpy(x.d, x.h, x.n, hipMemcpyHostToDevice)
                                 : hipMemcpyAsync(x.d, x.h, x.n, hipMemcpyHostToDevice, stream);
             if (e != hipSuccess) return fail(TQP_ERR_HIP, "batch descriptor upload: %s", hipGetErrorString(e));
         }
+        return TQP_OK;
+    };
+    if (b->direct) {
+        const DirectPlan& dp = b->dp;
+        return upload({{dp.d_frags, dp.frags.data(), sizeof(FlagsDirect) * dp.frags.size()},
+                       {dp.d_dim_items, dp.dim_items.data(), sizeof(FlagsItem) * dp.dim_items.size()},
+                       {dp.d_fact_items, dp.fact_items.data(), sizeof(FlagsItem) * dp.fact_items.size()}});
+    }
+    for (int c = 0; c < NCAND; ++c) {
+        if (!(b->cand_mask & (1 << c))) continue;
+        CandPlan& cp = b->cand[c];
+        HostTables& ht = (*b->host)[c];
+        const tqp_status st = upload({{cp.d_segs, ht.segs.data(), sizeof(BatchSeg) * S},
+                                      {cp.d_frags, ht.frags.data(), sizeof(BatchFrag) * nf},
+                                      {cp.d_hist_prefix, ht.hist_prefix.data(), sizeof(int64_t) * (S + 1)},
+                                      {cp.d_pass_prefix, ht.pass_prefix.data(), sizeof(int64_t) * 8 * (S + 1)},
+                                      {cp.d_join_prefix, ht.join_prefix.data(), sizeof(int64_t) * (nf + 1)}});
+        if (st != TQP_OK) return st;
     }
     return TQP_OK;
 }
@@ -542,6 +607,12 @@ tqp_status launch_candidate(tqp_batch* b, int c, hipStream_t s) {
 
 tqp_status run_candidate(tqp_batch* b, int c, hipStream_t s) {
     tqp_status st = TQP_OK;
+    if (b->direct) {
+        DirectPlan& dp = b->dp;
+        if ((st = fill_zero(b->ws, dp.zero_bytes, s, b->ctx)) != TQP_OK) return st;
+        return flags_direct_batch(b->ctx, dp.d_frags, b->nf, dp.d_dim_items, (int64_t)dp.dim_items.size(),
+                                  dp.d_fact_items, (int64_t)dp.fact_items.size(), s);
+    }
     for_each_cand(c, [&](auto cfg) { st = launch_candidate<decltype(cfg)>(b, c, s); });
     return st;
 }
@@ -573,6 +644,7 @@ tqp_status batch_prepare(tqp_ctx* ctx, const tqp_flags_fragment* frags, const tq
     b->chosen = chosen;
     b->frags.assign(frags, frags + nf);
     b->outs.assign(outs, outs + nf);
+    b->direct = nf > 0 && std::all_of(frags, frags + nf, flags_direct_ok);
     const size_t need = plan_all(b, nullptr, nullptr);
     if (!ws) {
         *ws_bytes = need;
