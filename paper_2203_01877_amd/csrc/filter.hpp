@@ -8,6 +8,7 @@
 // from the device: d_n).
 #pragma once
 #include "dev.hpp"
+#include "host.hpp"
 #include "radix.hpp"
 
 namespace tqp {
@@ -46,12 +47,19 @@ struct FilterPreds {
     }
 };
 
-template <int BLOCK, int ITEMS>
+// Bound by HBM: the predicate columns, the lines of the carried column that
+// hold a kept row, and the outputs.  60M rows, a 4- and an 8-byte predicate
+// column and a carried column, 16% kept (about 1.05 GB): 275 us, where tiles of
+// one round took 325 and those with a branch around each carried value's read
+// 372.
+template <int BLOCK, int ITEMS, int ROUNDS>
 __global__ void __launch_bounds__(BLOCK)
 k_filter(FilterPreds fp, int64_t n, const int32_t* carry, int32_t* out_row, int32_t* out_carry,
          int64_t cap, int64_t* d_count, uint64_t* status, uint32_t* tile_counter, uint32_t* flags,
-         const int64_t* d_n = nullptr) {
-    constexpr int TILE = BLOCK * ITEMS, W = BLOCK / WAVE;
+         const int64_t* d_n) {
+    constexpr int W = BLOCK / WAVE, MASKS = ROUNDS * ITEMS;
+    constexpr int64_t TILE = (int64_t)BLOCK * MASKS;
+    __shared__ uint64_t s_mask[W][MASKS];      // survivors of each 64 rows
     __shared__ int64_t s_wave[W];
     __shared__ int64_t s_base;
     __shared__ uint32_t s_tile;
@@ -68,22 +76,26 @@ k_filter(FilterPreds fp, int64_t n, const int32_t* carry, int32_t* out_row, int3
         if (ntiles == 0 && tile == 0 && tid == 0) *d_count = 0;
         return;
     }
-    const int64_t chunk = tile * TILE + (int64_t)w * ITEMS * WAVE;
-    uint64_t m[ITEMS];
+    const int64_t chunk = tile * TILE + (int64_t)w * MASKS * WAVE;
     int64_t wc = 0;
-    int64_t idx[ITEMS];
-    bool ok[ITEMS];
+#pragma unroll 1
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int64_t r0 = chunk + (int64_t)r * ITEMS * WAVE;
+        int64_t idx[ITEMS];
+        bool ok[ITEMS];
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        const int64_t i = chunk + j * WAVE + l;
-        ok[j] = i < n;
-        idx[j] = ok[j] ? i : n - 1;       // n >= 1: the tile exists
-    }
-    fp.eval<ITEMS>(idx, ok);
+        for (int j = 0; j < ITEMS; ++j) {
+            const int64_t i = r0 + j * WAVE + l;
+            ok[j] = i < n;
+            idx[j] = ok[j] ? i : n - 1;       // n >= 1: the tile exists
+        }
+        fp.eval<ITEMS>(idx, ok);
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        m[j] = ballot(ok[j]);
-        wc += popc64(m[j]);
+        for (int j = 0; j < ITEMS; ++j) {
+            const uint64_t m = ballot(ok[j]);
+            if (l == 0) s_mask[w][r * ITEMS + j] = m;
+            wc += popc64(m);
+        }
     }
     if (l == 0) s_wave[w] = wc;
     __syncthreads();
@@ -103,18 +115,54 @@ k_filter(FilterPreds fp, int64_t n, const int32_t* carry, int32_t* out_row, int3
     }
     __syncthreads();
     int64_t pos = s_base + s_wave[w];
+#pragma unroll 1
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int64_t r0 = chunk + (int64_t)r * ITEMS * WAVE;
+        int64_t o[ITEMS];                      // output position, -1: none
+        int32_t c[ITEMS];
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        const int64_t i = chunk + j * WAVE + l;
-        if ((m[j] >> l) & 1) {
-            const int64_t o = pos + popc64(m[j] & lanemask_lt());
-            if (o < cap) {
-                out_row[o] = (int32_t)i;
-                if (out_carry) out_carry[o] = carry[i];
+        for (int j = 0; j < ITEMS; ++j) {
+            const uint64_t m = s_mask[w][r * ITEMS + j];
+            o[j] = pos + popc64(m & lanemask_lt());
+            if (!((m >> l) & 1) || o[j] >= cap) o[j] = -1;
+            pos += popc64(m);
+        }
+        if (out_carry) {
+            // rows that are out read the tile's first row: no branch between the loads
+#pragma unroll
+            for (int j = 0; j < ITEMS; ++j) c[j] = carry[o[j] >= 0 ? r0 + j * WAVE + l : tile * TILE];
+        }
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            if (o[j] >= 0) {
+                out_row[o[j]] = (int32_t)(r0 + j * WAVE + l);
+                if (out_carry) out_carry[o[j]] = c[j];
             }
         }
-        pos += popc64(m[j]);
     }
+}
+
+constexpr int FILTER_BLOCK = 256, FILTER_ITEMS = 16;
+constexpr int64_t FILTER_TILE = FILTER_BLOCK * FILTER_ITEMS;   // rows per look-back word
+
+// Long tiles of four rounds from six short ones per CU on: scan and filter of
+// 60M rows 686 us with long tiles against 732, of 16M 206 against 227, of 8M
+// 115 against 129; of 4M 70 against 68 and of 1M 46 against 34, where the long
+// tiles leave CUs without one.
+constexpr int FILTER_ROUNDS = 4;
+inline tqp_status filter_launch(tqp_ctx* ctx, hipStream_t s, const char* name, const FilterPreds& fp, int64_t n,
+                                const int32_t* carry, int32_t* out_row, int32_t* out_carry, int64_t cap,
+                                int64_t* d_count, uint64_t* status, uint32_t* counter, const int64_t* d_n = nullptr) {
+    if (n > FILTER_TILE * 6 * ctx->num_cus)
+        TQP_LAUNCH(ctx, s, name,
+                   (k_filter<FILTER_BLOCK, FILTER_ITEMS, FILTER_ROUNDS>
+                    <<<grid_for(n, FILTER_TILE * FILTER_ROUNDS, 0), FILTER_BLOCK, 0, s>>>(
+                        fp, n, carry, out_row, out_carry, cap, d_count, status, counter, ctx->d_err, d_n)));
+    else
+        TQP_LAUNCH(ctx, s, name,
+                   (k_filter<FILTER_BLOCK, FILTER_ITEMS, 1><<<grid_for(n, FILTER_TILE, 0), FILTER_BLOCK, 0, s>>>(
+                       fp, n, carry, out_row, out_carry, cap, d_count, status, counter, ctx->d_err, d_n)));
+    return TQP_OK;
 }
 
 }  // namespace tqp

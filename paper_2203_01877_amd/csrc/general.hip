@@ -50,7 +50,6 @@ namespace tqp {
 namespace {
 
 using JCfgGen = JoinCfg<256, 8, 4096>;
-constexpr int GF_FILTER_BLOCK = 256, GF_FILTER_ITEMS = 16;
 constexpr int GF_HEAD_BLOCK = 256, GF_HEAD_ITEMS = 8;
 constexpr int GF_AGG_BLOCK = 256;
 constexpr int GF_MAX_COLS = 64;
@@ -727,7 +726,7 @@ void gen_reserve(Arena& a, const tqp_fragment& f, const tqp_fragment_out& o, Gen
         b.jb = join_reserve<JCfgGen>(a, N);
         if (!b.kv) b.ri = a.scratch<int32_t>(J);
     } else {
-        const int64_t tiles = (N + GF_FILTER_BLOCK * GF_FILTER_ITEMS - 1) / (GF_FILTER_BLOCK * GF_FILTER_ITEMS);
+        const int64_t tiles = (N + FILTER_TILE - 1) / FILTER_TILE;
         b.fstatus = a.zero<uint64_t>(tiles);
         b.fcounter = a.zero<uint32_t>(1);
     }
@@ -1073,10 +1072,9 @@ tqp_status gen_launch(tqp_ctx* ctx, const tqp_fragment& f, const tqp_fragment_ou
             fp.op[0] = CMP_NE;
             fp.k[0] = 0;
         }
-        constexpr int64_t TILE = GF_FILTER_BLOCK * GF_FILTER_ITEMS;
-        TQP_LAUNCH(ctx, s, "fragment_rows",
-                   (k_filter<GF_FILTER_BLOCK, GF_FILTER_ITEMS><<<grid_for(N, TILE, 0), GF_FILTER_BLOCK, 0, s>>>(
-                       fp, N, nullptr, b.li, nullptr, J, b.d_join, b.fstatus, b.fcounter, ctx->d_err)));
+        if ((st = filter_launch(ctx, s, "fragment_rows", fp, N, nullptr, b.li, nullptr, J, b.d_join, b.fstatus,
+                                b.fcounter)) != TQP_OK)
+            return st;
     }
     if (o.d_join) TQP_TRY_HIP(hipMemcpyAsync(o.d_join, b.d_join, 8, hipMemcpyDeviceToDevice, s));
     int32_t* li = b.li;

@@ -20,8 +20,7 @@
 namespace tqp {
 namespace {
 
-constexpr int NA_BLOCK = 256, NA_ITEMS = 16;
-constexpr int64_t NA_TILE = NA_BLOCK * NA_ITEMS;
+constexpr int64_t NA_TILE = FILTER_TILE;       // rows per status word
 constexpr size_t NA_COUNTER_BYTES = 256;       // the tile counter, then the status words
 constexpr int64_t NA_MAX_TILES = (TQP_NOALLOC_SCRATCH_BYTES - NA_COUNTER_BYTES) / 8;
 static_assert(NA_MAX_TILES * NA_TILE == TQP_FILTER_NOALLOC_MAX_ROWS, "header limit matches the scratch layout");
@@ -95,8 +94,6 @@ extern "C" tqp_status tqp_filter_noalloc(tqp_ctx* ctx, const tqp_column* cols, i
     // counter and the status words of this call's tiles start at zero
     tqp_status st = fill_zero(base, NA_COUNTER_BYTES + (size_t)((tiles * 8 + 15) & ~int64_t(15)), stream, ctx);
     if (st != TQP_OK) return st;
-    TQP_LAUNCH(ctx, stream, "filter_noalloc",
-               k_filter<NA_BLOCK, NA_ITEMS><<<grid_for(n, NA_TILE, 0), NA_BLOCK, 0, stream>>>(
-                   fp, n, carry, out_rowid, out_carry, cap, d_count, status, counter, ctx->d_err));
-    return TQP_OK;
+    return filter_launch(ctx, stream, "filter_noalloc", fp, n, carry, out_rowid, out_carry, cap, d_count, status,
+                         counter);
 }

@@ -16,7 +16,6 @@ constexpr int64_t GB_BUCKET_MIN_ROWS = 2048;
 
 using JCfg = JoinCfg<256, 8, 4096>;
 using SCfg = SegCfg<256, 16>;
-constexpr int FILTER_BLOCK = 256, FILTER_ITEMS = 16;
 
 // ---------------------------------------------------------------- top-k plan
 // Chunk levels for the worst case (every group survives the filter): level l
@@ -123,8 +122,7 @@ tqp_status tqp_filter(tqp_ctx* ctx, const tqp_column* cols, int ncols, int64_t n
         fp.op[p] = q.op;
         fp.k[p] = q.k;
     }
-    constexpr int TILE = FILTER_BLOCK * FILTER_ITEMS;
-    const int64_t tiles = (n + TILE - 1) / TILE;
+    const int64_t tiles = (n + FILTER_TILE - 1) / FILTER_TILE;
     uint64_t* status = nullptr;
     uint32_t* counter = nullptr;
     Arena a;
@@ -135,10 +133,7 @@ tqp_status tqp_filter(tqp_ctx* ctx, const tqp_column* cols, int ncols, int64_t n
     tqp_status st = with_workspace(ctx, ws, ws_bytes, stream, plan, a);
     if (st != TQP_OK || !ws) return st;
     if ((st = fill_zero(a.base, a.zsize, stream, ctx)) != TQP_OK) return st;
-    TQP_LAUNCH(ctx, stream, "filter",
-               k_filter<FILTER_BLOCK, FILTER_ITEMS><<<grid_for(n, TILE, 0), FILTER_BLOCK, 0, stream>>>(
-                   fp, n, carry, out_rowid, out_carry, cap, d_count, status, counter, ctx->d_err));
-    return TQP_OK;
+    return filter_launch(ctx, stream, "filter", fp, n, carry, out_rowid, out_carry, cap, d_count, status, counter);
 }
 
 tqp_status tqp_sort(tqp_ctx* ctx, const int32_t* keys, const int32_t* vals, int64_t n, const int64_t* d_n,

@@ -65,3 +65,25 @@ def test_noalloc_empty_and_limit(hip, ctx):
     with pytest.raises(hip.TQPError):
         hip.filter_noalloc(ctx, big, [(0, hip.TQP_LT, 5)], out, cnt, n=hip._lib.FILTER_NOALLOC_MAX_ROWS + 1)
     assert ctx.errors() == 0
+
+
+@pytest.mark.parametrize("n", [1, 4095, 4096, 4097, 300_001, 6_500_017])
+@pytest.mark.parametrize("keep", [0, 1, 2557])
+def test_filter_carry_edges(hip, ctx, n, keep):
+    """Tiles without a kept row, with some and with all of them, short and long tiles (6.5M rows), and a
+    capacity below the count: the carried value of every kept row and nothing else is written."""
+    import torch
+    host, dev, carry_h, carry_d = _cols(hip, n, 900 + n)
+    preds = [(0, hip.TQP_LT, keep)]
+    want = oracle.filter_rows([host[0]], preds)
+    for cap in (n, len(want) // 2):
+        out = torch.full((max(1, cap),), -7, dtype=torch.int32, device="cuda")[:cap]
+        outc = torch.full((max(1, cap),), -7, dtype=torch.int32, device="cuda")[:cap]
+        cnt = torch.full((1,), -7, dtype=torch.int64, device="cuda")
+        hip.filter_noalloc(ctx, dev[:1], preds, out, cnt, carry=carry_d, out_carry=outc)
+        k = min(cap, len(want))
+        assert int(cnt.item()) == len(want)
+        assert np.array_equal(out[:k].cpu().numpy(), want[:k])
+        assert np.array_equal(outc[:k].cpu().numpy(), carry_h[want[:k]])
+        assert (outc[k:].cpu().numpy() == -7).all()
+        assert ctx.errors() == (hip.DEVERR_CAPACITY if cap < len(want) else 0)
