@@ -5,6 +5,7 @@
 
 #include "flags_direct.hpp"
 #include "fragment.hpp"
+#include "tablejoin.hpp"
 
 namespace tqp {
 
@@ -295,13 +296,13 @@ tqp_status cust_launch(tqp_ctx* ctx, const tqp_cust_fragment& f, const tqp_cust_
     const AV* gv = reinterpret_cast<const AV*>(b.gvals);
     if (b.lowb <= BUCKET_SMALL_LOWB) {
         TQP_LAUNCH(ctx, s, "bucket_agg",
-                   (k_bucket_agg<256, 1 << BUCKET_SMALL_LOWB, AV><<<(unsigned)b.nbuckets, 256, 0, s>>>(
-                       b.gkeys, gv, b.bstarts, bhist, b.lowb, b.nbuckets, b.sstatus, b.scounter, so, ctx->d_err,
+                   (k_bucket_agg<256, 1 << BUCKET_SMALL_LOWB, SortedRows<AV>><<<(unsigned)b.nbuckets, 256, 0, s>>>(
+                       SortedRows<AV>{b.gkeys, gv, b.bstarts, bhist}, b.lowb, b.nbuckets, b.sstatus, b.scounter, so, ctx->d_err,
                        b.topk.filtered, b.topk.d_nf, f.k)));
     } else {
         TQP_LAUNCH(ctx, s, "bucket_agg",
-                   (k_bucket_agg<1024, 1 << BUCKET_LOWB_MAX, AV><<<(unsigned)b.nbuckets, 1024, 0, s>>>(
-                       b.gkeys, gv, b.bstarts, bhist, b.lowb, b.nbuckets, b.sstatus, b.scounter, so, ctx->d_err,
+                   (k_bucket_agg<1024, 1 << BUCKET_LOWB_MAX, SortedRows<AV>><<<(unsigned)b.nbuckets, 1024, 0, s>>>(
+                       SortedRows<AV>{b.gkeys, gv, b.bstarts, bhist}, b.lowb, b.nbuckets, b.sstatus, b.scounter, so, ctx->d_err,
                        b.topk.filtered, b.topk.d_nf, f.k)));
     }
     // ORDER BY sum DESC, custkey ASC LIMIT k, over the buckets' candidates
@@ -309,6 +310,93 @@ tqp_status cust_launch(tqp_ctx* ctx, const tqp_cust_fragment& f, const tqp_cust_
         TQP_OK)
         return st;
     return TQP_OK;
+}
+
+// The custkey fragment with its join by a key table (tablejoin.hpp).
+template <class VT>
+struct CustTable {
+    TableJoin<VT> tj;
+    int64_t nbuckets = 0;
+    uint64_t* sstatus = nullptr;
+    uint32_t* scounter = nullptr;
+    TopkBufs topk;
+};
+
+template <class VT>
+void cust_table_reserve(Arena& a, const tqp_ctx* ctx, const tqp_cust_fragment& f, const tqp_cust_out& o,
+                        CustTable<VT>& b, int spread) {
+    table_join_reserve(a, ctx, b.tj, f.n_fact, f.n_mid, norm_key_bits(f.key_bits), norm_key_bits(f.cust_bits),
+                       f.join_cap, f.mid_sorted != 0, spread);
+    b.nbuckets = int64_t(1) << b.tj.grp.part_bits;
+    b.sstatus = a.zero<uint64_t>(b.nbuckets);
+    b.scounter = a.zero<uint32_t>(1);
+    // top-k candidates: the first k groups of every bucket (at most the groups)
+    b.topk = topk_reserve(a, std::min<int64_t>(o.gcap, b.nbuckets * f.k), f.k);
+}
+
+// The table where it applies, and where it needs no more scratch than the
+// sorts it replaces (a caller's memory bound that admitted the fragment still
+// does): the spread of its partitions, 0 for the sorts.  Decided by the fragment
+// alone, so that the plan reported is the one run: the top-k's candidates are
+// bounded by gcap on both sides, so no gcap between the two compared makes the
+// table the larger one.
+template <class VT>
+int cust_table_fits(const tqp_ctx* ctx, const tqp_cust_fragment& f) {
+    if (!table_join_ok(ctx, f.n_fact, f.n_mid, norm_key_bits(f.key_bits), norm_key_bits(f.cust_bits))) return 0;
+    for (int spread : TJ_SPREADS) {
+        bool fits = true;
+        for (int64_t gcap : {int64_t(0), int64_t(1) << norm_key_bits(f.cust_bits)}) {
+            tqp_cust_out o{};
+            o.gcap = gcap;
+            Arena sorts, table;
+            CustBufs<R8, VT> s;
+            CustTable<VT> t;
+            cust_reserve<R8, VT>(sorts, f, o, s);
+            cust_table_reserve(table, ctx, f, o, t, spread);
+            fits = fits && table.total() <= sorts.total();
+        }
+        if (fits) return spread;
+    }
+    return 0;
+}
+int cust_table_spread(const tqp_ctx* ctx, const tqp_cust_fragment& f) {
+    return f.revenue_bits == 32 ? cust_table_fits<uint32_t>(ctx, f) : cust_table_fits<uint64_t>(ctx, f);
+}
+
+template <class VT>
+tqp_status cust_table_launch(tqp_ctx* ctx, const tqp_cust_fragment& f, const tqp_cust_out& o, const CustTable<VT>& b,
+                             hipStream_t s) {
+    tqp_status st;
+    // One stream: the mid side's kernels and the fact partition are bound by
+    // HBM alike, and the table's blocks take a CU's LDS each, so that beside
+    // the fact partition they wait for it (60M x 15M rows: 1409 us on two
+    // streams, 1279 on one; 3M x 750k rows 129 and 116).
+    if (f.mid_sorted)
+        st = table_build_sorted(ctx, s, b.tj.t, reinterpret_cast<const uint32_t*>(f.pk),
+                                reinterpret_cast<const uint32_t*>(f.custkey), f.n_mid);
+    else
+        st = table_build(ctx, s, b.tj.t, SrcKeyCol{f.pk, f.custkey, f.n_mid}, f.n_mid, "mid_part");
+    if (st != TQP_OK) return st;
+    // date < D and the revenue price * (100 - disc) evaluated as the row is read
+    SrcFilterRevenue<VT> fsrc{f.fk, f.date, f.price, f.disc, CMP_LT, f.D, f.n_fact, nullptr};
+    if ((st = table_partition(ctx, s, b.tj, fsrc, f.n_fact, "fact_part")) != TQP_OK) return st;
+    if ((st = table_probe(ctx, s, b.tj, fsrc, f.n_fact, "probe", "probe_lists")) != TQP_OK) return st;
+    // group-by: one block per bucket of custkeys, its first k groups as top-k candidates
+    using AV = typename std::conditional<sizeof(VT) == 8, int64_t, uint32_t>::type;
+    using Rows = ChunkRows<AV, VT>;
+    SegOut so{o.key, o.sum, o.cnt, nullptr, o.gcap, o.d_ngroups};
+    auto agg = [&](auto kern, int block) -> tqp_status {
+        TQP_LAUNCH(ctx, s, "bucket_agg",
+                   kern<<<(unsigned)b.nbuckets, block, 0, s>>>(Rows{b.tj.grp, o.d_join}, b.tj.lowb, b.nbuckets,
+                                                              b.sstatus, b.scounter, so, ctx->d_err, b.topk.filtered,
+                                                              b.topk.d_nf, f.k));
+        return TQP_OK;
+    };
+    st = b.tj.lowb <= BUCKET_SMALL_LOWB ? agg(k_bucket_agg<256, 1 << BUCKET_SMALL_LOWB, Rows>, 256)
+                                        : agg(k_bucket_agg<1024, 1 << BUCKET_LOWB_MAX, Rows>, 1024);
+    if (st != TQP_OK) return st;
+    // ORDER BY sum DESC, custkey ASC LIMIT k, over the buckets' candidates
+    return topk_launch_candidates(b.topk, o.cnt, f.k, o.top_key, o.top_sum, o.top_cnt, o.d_topk, s, ctx);
 }
 
 tqp_status check_cust(const tqp_cust_fragment* f, const tqp_cust_out* o) {
@@ -355,6 +443,23 @@ tqp_status tqp_fragment_cust_plan(tqp_ctx* ctx, const tqp_cust_fragment* f, int*
                                   int* mid_passes, int* group_passes, int* group_lowb) {
     clear_error();
     if (!ctx || !f) return fail(TQP_ERR_INVALID, "null argument");
+    if (const int spread = cust_table_spread(ctx, *f)) {
+        // the join by a key table: one pass partitions each side, by the key
+        // bits above fact_lowb, and the probe partitions its output
+        auto report = [&](auto vt) {
+            CustTable<decltype(vt)> b;
+            Arena a;
+            cust_table_reserve(a, ctx, *f, tqp_cust_out{}, b, spread);
+            if (fact_passes) *fact_passes = b.tj.fact_bits ? 1 : 0;
+            if (fact_lowb) *fact_lowb = b.tj.t.key_bits - b.tj.fact_bits;
+            if (mid_passes) *mid_passes = f->mid_sorted ? 0 : 1;
+            if (group_passes) *group_passes = 1;
+            if (group_lowb) *group_lowb = b.tj.lowb;
+        };
+        if (f->revenue_bits == 32) report(uint32_t{});
+        else report(uint64_t{});
+        return TQP_OK;
+    }
     return with_radix_cfg(ctx->digit_bits, [&](auto cfg) -> tqp_status {
         using Cfg = decltype(cfg);
         tqp_cust_out o{};
@@ -376,6 +481,18 @@ tqp_status tqp_fragment_cust(tqp_ctx* ctx, const tqp_cust_fragment* f, const tqp
     if (!ctx) return fail(TQP_ERR_INVALID, "null context");
     tqp_status st = check_cust(f, o);
     if (st != TQP_OK) return st;
+    if (const int spread = cust_table_spread(ctx, *f)) {
+        auto run = [&](auto vt) -> tqp_status {
+            CustTable<decltype(vt)> b;
+            Arena a;
+            auto plan = [&](Arena& ar) { cust_table_reserve(ar, ctx, *f, *o, b, spread); };
+            tqp_status s2 = with_workspace(ctx, ws, ws_bytes, stream, plan, a);
+            if (s2 != TQP_OK || !ws) return s2;
+            if ((s2 = fill_zero(a.base, a.zsize, stream, ctx)) != TQP_OK) return s2;
+            return cust_table_launch(ctx, *f, *o, b, stream);
+        };
+        return f->revenue_bits == 32 ? run(uint32_t{}) : run(uint64_t{});
+    }
     return with_radix_cfg(ctx->digit_bits, [&](auto cfg) -> tqp_status {
         using Cfg = decltype(cfg);
         auto run = [&](auto vt) -> tqp_status {

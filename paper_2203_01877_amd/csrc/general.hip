@@ -45,6 +45,7 @@
 // counts.
 #include "filter.hpp"
 #include "fragment.hpp"
+#include "tablejoin.hpp"
 
 namespace tqp {
 namespace {
@@ -580,6 +581,9 @@ struct GenBufs {
     int32_t* fval32 = nullptr;
     GenKv<Cfg, uint64_t> kv64;
     GenKv<Cfg, uint32_t> kv32;
+    bool table = false;                      // its join by a key table (tablejoin.hpp) instead of the sorts
+    TableJoin<uint64_t> tj64;
+    TableJoin<uint32_t> tj32;
     JoinBufs jb;
     uint32_t *fsk = nullptr, *fsv = nullptr, *dsk = nullptr, *dsv = nullptr;
     uint64_t* fstatus = nullptr;             // no join: the compaction of the kept fact rows
@@ -605,7 +609,8 @@ int gf_group_bits(const tqp_fragment& f) {
 }
 
 template <class Cfg>
-void gen_reserve(Arena& a, const tqp_fragment& f, const tqp_fragment_out& o, GenBufs<Cfg>& b) {
+void gen_reserve(Arena& a, const tqp_ctx* ctx, const tqp_fragment& f, const tqp_fragment_out& o, GenBufs<Cfg>& b,
+                 int spread) {
     const int kb = norm_key_bits(f.key_bits);
     const int64_t N = f.n_fact, J = f.join_cap;
     b.join = f.fact_key >= 0;
@@ -676,10 +681,22 @@ void gen_reserve(Arena& a, const tqp_fragment& f, const tqp_fragment_out& o, Gen
         b.reads_fact = group_f || prog_f;
         b.kv = b.bucket && b.fpush && b.dpush >= 0 && f.n_group == 1;
         b.v32 = b.kv && f.value_bits == 32;
+        b.table = spread && b.kv && table_join_ok(ctx, N, f.n_dim, kb, b.gbits);
     }
     if (f.n_fact_pred > 0) b.fkeep = a.scratch<uint8_t>(N);
-    if (b.join) {
-        if (f.n_dim_pred > 0) b.dkeep = a.scratch<uint8_t>(f.n_dim);
+    if (b.join && f.n_dim_pred > 0) b.dkeep = a.scratch<uint8_t>(f.n_dim);
+    if (b.table) {
+        if (b.v32) {
+            b.fval32 = a.scratch<int32_t>(N);
+            table_join_reserve(a, ctx, b.tj32, N, f.n_dim, kb, b.gbits, J, false, spread);
+            b.lowb = b.tj32.lowb;
+        } else {
+            b.fval = a.scratch<int64_t>(N);
+            table_join_reserve(a, ctx, b.tj64, N, f.n_dim, kb, b.gbits, J, false, spread);
+            b.lowb = b.tj64.lowb;
+        }
+        b.nbuckets = int64_t(1) << (b.gbits - b.lowb);
+    } else if (b.join) {
         b.flowb = join_low_bits(N, kb, Cfg::RADIX_BITS, JCfgGen::TILE, JCfgGen::RWIN);
         if (b.flowb > FINISH_LOG2) b.flowb = FINISH_LOG2;
         // the fact sorts' first pass looks back instead of reading per-tile
@@ -748,7 +765,7 @@ void gen_reserve(Arena& a, const tqp_fragment& f, const tqp_fragment_out& o, Gen
         b.ri2 = a.scratch<int32_t>(J);
     }
     if (!b.kv) b.gkey = a.scratch<uint32_t>(J);
-    for (int k = 0; k < f.n_agg; ++k)
+    for (int k = 0; k < f.n_agg && !b.table; ++k)
         if (f.aggs[k].op != TQP_AGG_COUNT) b.vals[k] = b.fpush && k == b.vsort ? b.jval : a.scratch<int64_t>(J);
     if (b.distinct >= 0) {
         b.sa = radix_reserve<Cfg, uint32_t>(a, J, 32);
@@ -823,10 +840,9 @@ struct JoinedCols {
 // the fragment has a top-k.  Groups come out in ascending key order, as from
 // the full sort.  bhist: the digit counts of a one-pass group sort (the
 // buckets), else the bucket starts are searched for.
-template <class Cfg, class AV>
+template <class Cfg, class Rows>
 tqp_status bucket_groupby(tqp_ctx* ctx, const tqp_fragment& f, const tqp_fragment_out& o, const GenBufs<Cfg>& b,
-                          const uint32_t* keys, const AV* vals, const uint32_t* bhist, hipStream_t s) {
-    const int64_t J = f.join_cap;
+                          const Rows& rows, hipStream_t s) {
     const int vop = f.aggs[b.vsort].op;
     int64_t* vout = vop == TQP_AGG_AVG ? b.bval : static_cast<int64_t*>(f.aggs[b.vsort].out);
     int64_t* cout = b.bcnt;
@@ -839,32 +855,26 @@ tqp_status bucket_groupby(tqp_ctx* ctx, const tqp_fragment& f, const tqp_fragmen
         finish |= f.aggs[k].op == TQP_AGG_AVG;
     }
     SegOut so{o.key, vout, cout, nullptr, o.gcap, o.d_ngroups};
-    if (!bhist) {
-        TQP_LAUNCH(ctx, s, "fragment_bucket_bounds",
-                   k_bucket_bounds<<<grid_for(b.nbuckets + 1, 256, 0), 256, 0, s>>>(keys, J, b.d_join, b.lowb,
-                                                                                      b.nbuckets, b.bstarts));
-    }
     TopCand* cand = f.topk > 0 ? b.topk.filtered : nullptr;
     int64_t* d_cand = f.topk > 0 ? b.topk.d_nf : nullptr;
     const bool bycnt = f.topk > 0 && f.aggs[0].op == TQP_AGG_COUNT;
     constexpr int SLOTS = 1 << BUCKET_LOWB_MAX;
     auto go = [&](auto kern) -> tqp_status {
         TQP_LAUNCH(ctx, s, "fragment_bucket_agg",
-                   kern<<<(unsigned)b.nbuckets, 1024, 0, s>>>(keys, vals, b.bstarts, bhist, b.lowb, b.nbuckets,
-                                                              b.bstatus, b.bcounter, so, ctx->d_err, cand, d_cand,
-                                                              f.topk));
+                   kern<<<(unsigned)b.nbuckets, 1024, 0, s>>>(rows, b.lowb, b.nbuckets, b.bstatus, b.bcounter, so,
+                                                              ctx->d_err, cand, d_cand, f.topk));
         return TQP_OK;
     };
     tqp_status st;
     if (vop == TQP_AGG_MIN)
-        st = bycnt ? go(k_bucket_agg<1024, SLOTS, AV, BUCKET_MIN, true>)
-                   : go(k_bucket_agg<1024, SLOTS, AV, BUCKET_MIN, false>);
+        st = bycnt ? go(k_bucket_agg<1024, SLOTS, Rows, BUCKET_MIN, true>)
+                   : go(k_bucket_agg<1024, SLOTS, Rows, BUCKET_MIN, false>);
     else if (vop == TQP_AGG_MAX)
-        st = bycnt ? go(k_bucket_agg<1024, SLOTS, AV, BUCKET_MAX, true>)
-                   : go(k_bucket_agg<1024, SLOTS, AV, BUCKET_MAX, false>);
+        st = bycnt ? go(k_bucket_agg<1024, SLOTS, Rows, BUCKET_MAX, true>)
+                   : go(k_bucket_agg<1024, SLOTS, Rows, BUCKET_MAX, false>);
     else
-        st = bycnt ? go(k_bucket_agg<1024, SLOTS, AV, BUCKET_SUM, true>)
-                   : go(k_bucket_agg<1024, SLOTS, AV, BUCKET_SUM, false>);
+        st = bycnt ? go(k_bucket_agg<1024, SLOTS, Rows, BUCKET_SUM, true>)
+                   : go(k_bucket_agg<1024, SLOTS, Rows, BUCKET_SUM, false>);
     if (st != TQP_OK) return st;
     if (finish && o.gcap > 0) {
         AggSet as{};
@@ -881,6 +891,19 @@ tqp_status bucket_groupby(tqp_ctx* ctx, const tqp_fragment& f, const tqp_fragmen
     if (f.topk > 0)
         return topk_launch_candidates(b.topk, cout, f.topk, o.top_key, o.top_val, b.tcnt, o.d_topk, s, ctx);
     return TQP_OK;
+}
+
+// The rows of a group sort as buckets: one search per bucket where the sort's
+// digit counts do not give them.
+template <class Cfg, class AV>
+tqp_status sorted_buckets(tqp_ctx* ctx, const tqp_fragment& f, const tqp_fragment_out& o, const GenBufs<Cfg>& b,
+                          const uint32_t* keys, const AV* vals, const uint32_t* bhist, hipStream_t s) {
+    if (!bhist) {
+        TQP_LAUNCH(ctx, s, "fragment_bucket_bounds",
+                   k_bucket_bounds<<<grid_for(b.nbuckets + 1, 256, 0), 256, 0, s>>>(keys, f.join_cap, b.d_join, b.lowb,
+                                                                                      b.nbuckets, b.bstarts));
+    }
+    return bucket_groupby<Cfg>(ctx, f, o, b, SortedRows<AV>{keys, vals, b.bstarts, bhist}, s);
 }
 
 // The one valued aggregate's program over every fact row, in row order (it
@@ -942,8 +965,44 @@ tqp_status kv_launch(tqp_ctx* ctx, const tqp_fragment& f, const tqp_fragment_out
                                     "fragment_sort_group", "fragment_sort_group")) != TQP_OK)
         return st;
     using AV = typename std::conditional<V32, int32_t, int64_t>::type;
-    return bucket_groupby<Cfg, AV>(ctx, f, o, b, k.gk, reinterpret_cast<const AV*>(k.gv),
+    return sorted_buckets<Cfg, AV>(ctx, f, o, b, k.gk, reinterpret_cast<const AV*>(k.gv),
                                    k.gsort.pd.npass == 1 ? k.gsort.hist : nullptr, s);
+}
+
+// The keyed bucket group-by with the join by a key table: the dim side's
+// predicate, partition and table on the side stream beside the fact side's
+// predicate, value program and partition; the probe writes (group key, value)
+// into the group partitions the buckets read.
+template <class Cfg, class V>
+tqp_status table_launch(tqp_ctx* ctx, const tqp_fragment& f, const tqp_fragment_out& o, const GenBufs<Cfg>& b,
+                        const TableJoin<V>& tj, hipStream_t s) {
+    constexpr bool V32 = sizeof(V) == 4;
+    const int64_t N = f.n_fact;
+    const int32_t* fkey = static_cast<const int32_t*>(f.fact_cols[f.fact_key].data);
+    tqp_status st;
+    if ((st = side_fork(ctx, s)) != TQP_OK) return st;
+    if (b.dkeep && f.n_dim > 0 &&
+        (st = eval_program(ctx, f.dim_cols, nullptr, f.n_dim_cols, f.n_dim, nullptr, f.dim_pred, f.n_dim_pred, b.dkeep,
+                           ctx->side, "tqp_fragment_run", "fragment_dim_pred", XOUT_FLAG)) != TQP_OK)
+        return st;
+    SrcKeepCol ds{static_cast<const int32_t*>(f.dim_cols[f.dim_key].data), b.dkeep,
+                  static_cast<const int32_t*>(f.dim_cols[b.dpush].data), f.n_dim};
+    if ((st = table_build(ctx, ctx->side, tj.t, ds, f.n_dim, "fragment_part_dim")) != TQP_OK) return st;
+    if (b.fkeep && N > 0 &&
+        (st = eval_program(ctx, f.fact_cols, nullptr, f.n_fact_cols, N, nullptr, f.fact_pred, f.n_fact_pred, b.fkeep,
+                           s, "tqp_fragment_run", "fragment_fact_pred", XOUT_FLAG)) != TQP_OK)
+        return st;
+    void* fv = V32 ? static_cast<void*>(b.fval32) : static_cast<void*>(b.fval);
+    if (N > 0 && (st = fact_value(ctx, f, b, fv, V32 ? XOUT_I32 : XOUT_I64, s)) != TQP_OK) return st;
+    auto rows = [&] {
+        if constexpr (V32) return SrcKeepCol{fkey, b.fkeep, b.fval32, N};
+        else return SrcKeepVal64{fkey, b.fkeep, b.fval, N};
+    }();
+    if ((st = table_partition(ctx, s, tj, rows, N, "fragment_part_fact")) != TQP_OK) return st;
+    if ((st = side_join(ctx, s)) != TQP_OK) return st;
+    if ((st = table_probe(ctx, s, tj, rows, N, "fragment_probe", "fragment_probe_lists")) != TQP_OK) return st;
+    using AV = typename std::conditional<V32, int32_t, int64_t>::type;
+    return bucket_groupby<Cfg>(ctx, f, o, b, ChunkRows<AV, V>{tj.grp, o.d_join}, s);
 }
 
 // The direct group-by over the packed keys and the aggregates' values of the
@@ -987,6 +1046,9 @@ tqp_status gen_launch(tqp_ctx* ctx, const tqp_fragment& f, const tqp_fragment_ou
                       hipStream_t s) {
     const int kb = norm_key_bits(f.key_bits);
     const int64_t N = f.n_fact, J = f.join_cap;
+    if (b.table)
+        return b.v32 ? table_launch<Cfg, uint32_t>(ctx, f, o, b, b.tj32, s)
+                     : table_launch<Cfg, uint64_t>(ctx, f, o, b, b.tj64, s);
     tqp_status st;
     // 1. predicates and 2. the join's sorts.  With a join the dim side (its
     // predicate, its sort and the finishing pass) runs on the side stream
@@ -1152,7 +1214,7 @@ tqp_status gen_launch(tqp_ctx* ctx, const tqp_fragment& f, const tqp_fragment_ou
         if ((st = radix_launch<Cfg, uint64_t>(b.sv, a3, J, true, nullptr, key_mask_for(b.gbits), b.kc, b.vc, ctx, s,
                                               "fragment_sort_group", "fragment_sort_group")) != TQP_OK)
             return st;
-        return bucket_groupby<Cfg, int64_t>(ctx, f, o, b, b.kc, reinterpret_cast<const int64_t*>(b.vc),
+        return sorted_buckets<Cfg, int64_t>(ctx, f, o, b, b.kc, reinterpret_cast<const int64_t*>(b.vc),
                                             b.sv.pd.npass == 1 ? b.sv.hist : nullptr, s);
     }
     if (b.vsort >= 0) {
@@ -1161,7 +1223,7 @@ tqp_status gen_launch(tqp_ctx* ctx, const tqp_fragment& f, const tqp_fragment_ou
                                               "fragment_sort_group", "fragment_sort_group")) != TQP_OK)
             return st;
         if (b.bucket)
-            return bucket_groupby<Cfg, int64_t>(ctx, f, o, b, b.kc, reinterpret_cast<const int64_t*>(b.vc),
+            return sorted_buckets<Cfg, int64_t>(ctx, f, o, b, b.kc, reinterpret_cast<const int64_t*>(b.vc),
                                                 b.sv.pd.npass == 1 ? b.sv.hist : nullptr, s);
     } else {
         SrcPermKey<0> a3{b.gkey, perm_in, J, b.d_join};
@@ -1291,9 +1353,23 @@ extern "C" tqp_status tqp_fragment_run(tqp_ctx* ctx, const tqp_fragment* f, cons
     }
     return with_radix_cfg(ctx->digit_bits, [&](auto cfg) -> tqp_status {
         using Cfg = decltype(cfg);
+        // the join by a key table where it needs no more scratch than the sorts
+        int spread = 0;
+        Arena sorts;
+        {
+            GenBufs<Cfg> g;
+            gen_reserve<Cfg>(sorts, ctx, fd, *o, g, 0);
+        }
+        for (int sp : TJ_SPREADS) {
+            GenBufs<Cfg> g;
+            Arena table;
+            gen_reserve<Cfg>(table, ctx, fd, *o, g, sp);
+            if (!g.table) break;
+            if (table.total() <= sorts.total()) { spread = sp; break; }
+        }
         GenBufs<Cfg> b;
         Arena a;
-        auto plan = [&](Arena& ar) { gen_reserve<Cfg>(ar, fd, *o, b); };
+        auto plan = [&](Arena& ar) { gen_reserve<Cfg>(ar, ctx, fd, *o, b, spread); };
         tqp_status s2 = with_workspace(ctx, ws, ws_bytes, stream, plan, a);
         if (s2 != TQP_OK || !ws) return s2;
         if ((s2 = fill_zero(a.base, a.zsize, stream, ctx)) != TQP_OK) return s2;

@@ -281,9 +281,9 @@ tqp_status tqp_groupby_agg(tqp_ctx* ctx, const int32_t* gkey, int64_t n, const i
                                                                                             bstarts));
                 SegOut o{out_key, out_sum, out_cnt, nullptr, gcap, d_ngroups};
                 TQP_LAUNCH(ctx, stream, "groupby_bucket_agg",
-                           (k_bucket_agg<1024, 1 << BUCKET_LOWB_MAX, int64_t><<<(unsigned)nb, 1024, 0, stream>>>(
-                               skeys, reinterpret_cast<const int64_t*>(svals), bstarts, bhist, lowb, nb, bstatus,
-                               bcounter, o, ctx->d_err)));
+                           (k_bucket_agg<1024, 1 << BUCKET_LOWB_MAX, SortedRows<int64_t>><<<(unsigned)nb, 1024, 0, stream>>>(
+                               SortedRows<int64_t>{skeys, reinterpret_cast<const int64_t*>(svals), bstarts, bhist},
+                               lowb, nb, bstatus, bcounter, o, ctx->d_err)));
                 return TQP_OK;
             });
         // One value column: sort it alongside the keys (8-byte payload), so

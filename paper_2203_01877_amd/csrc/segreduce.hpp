@@ -11,6 +11,7 @@
 // a run cut by a chunk boundary are added atomically into zeroed outputs
 // (integer adds, so the result does not depend on their order).
 #pragma once
+#include "chunks.hpp"
 #include "dev.hpp"
 #include "topk.hpp"
 
@@ -226,22 +227,146 @@ constexpr int BUCKET_LOWB_MAX = 13;        // 8192 slots: 96 KB of LDS
 __global__ void k_bucket_bounds(const uint32_t* keys, int64_t n_upper, const int64_t* d_n, int lowb,
                                 int64_t nbuckets, int64_t* starts);
 
-// vals: int64 values (VT = int64_t), int32 values (VT = int32_t) or values in
-// [0, 2^32) (VT = uint32_t).  OP: what the value column is reduced to (sum;
+// Where a bucket's rows are.  each(b, f) calls f(low key bits, value) for
+// every row of bucket b over the whole block.
+//
+// Rows sorted by the key bits above lowb: starts, or the digit counts of the
+// sort's single pass (bhist).
+template <class VT>
+struct SortedRows {
+    using Value = VT;
+    const uint32_t* keys;
+    const VT* vals;
+    const int64_t* starts;
+    const uint32_t* bhist;
+    template <int BLOCK, class F>
+    __device__ __forceinline__ void each(int64_t b, int lowb, int64_t* s_base, F f) const {
+        constexpr int U = 8;                               // loads in flight per thread
+        const int tid = threadIdx.x, w = tid / WAVE, l = lane_id();
+        int64_t lo, hi;
+        if (bhist) {
+            // bucket b = digit b of the single sort pass: it starts after the
+            // elements of the smaller digits
+            if (w == 0) {
+                int64_t acc = 0;
+                for (int64_t d = l; d < b; d += WAVE) acc += bhist[d];
+                acc = wave_sum(acc);
+                if (l == 0) *s_base = acc;
+            }
+            __syncthreads();
+            lo = *s_base;
+            hi = lo + bhist[b];
+            __syncthreads();
+        } else {
+            lo = starts[b];
+            hi = starts[b + 1];
+        }
+        const uint32_t lmask = (1u << lowb) - 1;
+        for (int64_t i0 = lo + tid; i0 < hi; i0 += (int64_t)BLOCK * U) {
+            uint32_t k[U];
+            VT v[U];
+#pragma unroll
+            for (int j = 0; j < U; ++j) {          // clamped index: no branch between the loads
+                const int64_t i = i0 + (int64_t)j * BLOCK;
+                const int64_t ic = i < hi ? i : hi - 1;
+                k[j] = keys[ic] & lmask;
+                v[j] = vals[ic];
+            }
+#pragma unroll
+            for (int j = 0; j < U; ++j)
+                if (i0 + (int64_t)j * BLOCK < hi) f(k[j], v[j]);
+        }
+    }
+    __device__ __forceinline__ void finish(int64_t, uint32_t*) const {}
+};
+
+// Rows in the chunk list of a group partition (V: the value's bits).  A wave
+// takes a group of chunks at a time, four of them in flight; when they hold few rows
+// (a small input spread over many blocks), their rows laid end to end, so that
+// the lanes are full and all loads in flight.  finish: the rows claimed (a
+// join's size) go to *d_rows, more than the list keeps raise the capacity
+// flag.
+template <class VT, class V>
+struct ChunkRows {
+    using Value = VT;
+    Chunks<uint16_t, V> c;
+    int64_t* d_rows;                               // nullable
+    template <int BLOCK, class F>
+    __device__ __forceinline__ void each(int64_t b, int, int64_t*, F f) const {
+        constexpr int G = CHUNK_GROUP, PER = CHUNK / WAVE, U = 8;     // loads in flight per thread
+        constexpr uint32_t SPARSE = U * WAVE;      // rows of a group that one round of loads covers
+        const int w = threadIdx.x / WAVE, l = lane_id();
+        const uint32_t nc = c.dcount[b];
+        const uint32_t* dir = c.list + c.first[b];
+        uint32_t k[U];
+        V v[U];
+        bool in[U];
+        for (uint32_t c0 = w * G; c0 < nc; c0 += BLOCK / WAVE * G) {
+            uint32_t id = 0, rows = 0;
+            if (l < G && c0 + l < nc) {
+                id = dir[c0 + l];
+                rows = c.rows[id];
+            }
+            const uint32_t incl = wave_incl_sum(rows), total = wave_read(incl, WAVE - 1);
+            if (total <= SPARSE) {
+                const uint32_t first = incl - rows;
+#pragma unroll
+                for (int j = 0; j < U; ++j) {
+                    const uint32_t p = j * WAVE + l;
+                    int g = 0;                     // last chunk that starts at or before p
+#pragma unroll
+                    for (int step = G / 2; step >= 1; step >>= 1)
+                        if (wave_shfl(first, g + step) <= p) g += step;
+                    in[j] = p < total;
+                    // (every lane takes part in the permutes)
+                    const uint32_t chunk = wave_shfl(id, g), f0 = wave_shfl(first, g);
+                    const int64_t at = (int64_t)chunk * CHUNK + (in[j] ? p - f0 : 0);     // past the end: row 0
+                    k[j] = c.keys[at];
+                    v[j] = c.vals[at];
+                }
+#pragma unroll
+                for (int j = 0; j < U; ++j)
+                    if (in[j]) f(k[j], (VT)v[j]);
+                continue;
+            }
+            for (uint32_t q = 0; q < G && c0 + q < nc; q += U / PER) {
+#pragma unroll
+                for (int j = 0; j < U; ++j) {      // rows past the end read the chunk's first row
+                    const int64_t at = (int64_t)wave_read(id, q + j / PER) * CHUNK;
+                    const uint32_t r = (j % PER) * WAVE + l;
+                    in[j] = r < wave_read(rows, q + j / PER);
+                    k[j] = __builtin_nontemporal_load(&c.keys[at + (in[j] ? r : 0)]);
+                    v[j] = __builtin_nontemporal_load(&c.vals[at + (in[j] ? r : 0)]);
+                }
+#pragma unroll
+                for (int j = 0; j < U; ++j)
+                    if (in[j]) f(k[j], (VT)v[j]);
+            }
+        }
+    }
+    __device__ __forceinline__ void finish(int64_t b, uint32_t* flags) const {
+        if (b != 0 || threadIdx.x != 0) return;
+        const int64_t n = (int64_t)(*c.pool & POOL_ROW_MASK);
+        if (d_rows) *d_rows = n;
+        if (n > c.row_cap) set_flag(flags, FLAG_CAPACITY);
+    }
+};
+
+// VT: int64 values (int64_t), int32 values (int32_t) or values in [0, 2^32)
+// (uint32_t).  OP: what the value column is reduced to (sum;
 // min or max for signed values), written to out.sum.  With cand, each block also appends the first
 // k of its groups in the order value DESC (the count with BYCNT), key ASC
 // (step 1 of the top-k: the overall first k are among them) to cand,
 // counting them in *d_cand.
 enum : int { BUCKET_SUM = 0, BUCKET_MIN = 1, BUCKET_MAX = 2 };
-template <int BLOCK, int SLOTS, class VT = int64_t, int OP = BUCKET_SUM, bool BYCNT = false>
+template <int BLOCK, int SLOTS, class Rows, int OP = BUCKET_SUM, bool BYCNT = false>
 __global__ void __launch_bounds__(BLOCK)
-k_bucket_agg(const uint32_t* keys, const VT* vals, const int64_t* starts, const uint32_t* bhist, int lowb,
-             int64_t nbuckets, uint64_t* status, uint32_t* counter, SegOut out, uint32_t* flags,
-             TopCand* cand = nullptr, int64_t* d_cand = nullptr, int k = 0) {
+k_bucket_agg(Rows rows, int lowb, int64_t nbuckets, uint64_t* status, uint32_t* counter, SegOut out,
+             uint32_t* flags, TopCand* cand = nullptr, int64_t* d_cand = nullptr, int k = 0) {
+    using VT = typename Rows::Value;
     static_assert(SLOTS <= (1 << BUCKET_LOWB_MAX), "slot table larger than the LDS budget");
     static_assert(OP == BUCKET_SUM || std::is_same<VT, int64_t>::value || std::is_same<VT, int32_t>::value,
                   "min / max over signed values");
-    constexpr int U = 8;                               // loads in flight per thread
     constexpr int PER = (SLOTS + BLOCK - 1) / BLOCK;   // most slots per thread
     __shared__ unsigned long long s_sum[SLOTS];
     __shared__ uint32_t s_cnt[SLOTS];
@@ -259,54 +384,22 @@ k_bucket_agg(const uint32_t* keys, const VT* vals, const int64_t* starts, const 
     __syncthreads();
     const int64_t b = s_b;
     if (b >= nbuckets) return;
-    int64_t lo, hi;
-    if (bhist) {
-        // bucket b = digit b of the single sort pass: it starts after the
-        // elements of the smaller digits
-        if (w == 0) {
-            int64_t acc = 0;
-            for (int64_t d = l; d < b; d += WAVE) acc += bhist[d];
-            acc = wave_sum(acc);
-            if (l == 0) s_base = acc;
+    rows.template each<BLOCK>(b, lowb, &s_base, [&](uint32_t kk, VT v) {
+        if constexpr (OP == BUCKET_MIN) {
+            atomicMin(reinterpret_cast<long long*>(&s_sum[kk]), (long long)v);
+        } else if constexpr (OP == BUCKET_MAX) {
+            atomicMax(reinterpret_cast<long long*>(&s_sum[kk]), (long long)v);
+        } else if constexpr (std::is_same<VT, uint32_t>::value) {
+            // 32-bit add on the low word; a wrap carries into the high word
+            uint32_t* w2 = reinterpret_cast<uint32_t*>(&s_sum[kk]);
+            const uint32_t old = atomicAdd(&w2[0], v);
+            if (old + v < old) atomicAdd(&w2[1], 1u);
+        } else {
+            atomicAdd(&s_sum[kk], (unsigned long long)v);
         }
-        __syncthreads();
-        lo = s_base;
-        hi = lo + bhist[b];
-        __syncthreads();
-    } else {
-        lo = starts[b];
-        hi = starts[b + 1];
-    }
-    const uint32_t lmask = (uint32_t)slots - 1;
-    for (int64_t i0 = lo + tid; i0 < hi; i0 += (int64_t)BLOCK * U) {
-        uint32_t k[U];
-        VT v[U];
-#pragma unroll
-        for (int j = 0; j < U; ++j) {          // clamped index: no branch between the loads
-            const int64_t i = i0 + (int64_t)j * BLOCK;
-            const int64_t ic = i < hi ? i : hi - 1;
-            k[j] = keys[ic] & lmask;
-            v[j] = vals[ic];
-        }
-#pragma unroll
-        for (int j = 0; j < U; ++j) {
-            if (i0 + (int64_t)j * BLOCK < hi) {
-                if constexpr (OP == BUCKET_MIN) {
-                    atomicMin(reinterpret_cast<long long*>(&s_sum[k[j]]), (long long)v[j]);
-                } else if constexpr (OP == BUCKET_MAX) {
-                    atomicMax(reinterpret_cast<long long*>(&s_sum[k[j]]), (long long)v[j]);
-                } else if constexpr (std::is_same<VT, uint32_t>::value) {
-                    // 32-bit add on the low word; a wrap carries into the high word
-                    uint32_t* w2 = reinterpret_cast<uint32_t*>(&s_sum[k[j]]);
-                    const uint32_t old = atomicAdd(&w2[0], v[j]);
-                    if (old + v[j] < old) atomicAdd(&w2[1], 1u);
-                } else {
-                    atomicAdd(&s_sum[k[j]], (unsigned long long)v[j]);
-                }
-                atomicAdd(&s_cnt[k[j]], 1u);
-            }
-        }
-    }
+        atomicAdd(&s_cnt[kk], 1u);
+    });
+    rows.finish(b, flags);
     __syncthreads();
     // non-empty slots in ascending order -> local group index
     const int per = (slots + BLOCK - 1) / BLOCK;      // consecutive slots per thread
