@@ -51,6 +51,7 @@ struct Chunks {
     uint32_t* dcount = nullptr;        // [partitions] chunks of each partition (zero on entry)
     uint32_t* cursor = nullptr;        // [partitions] chunks listed (zero on entry)
     uint64_t* pool = nullptr;          // rows and chunks claimed (zero on entry)
+    uint32_t* open = nullptr;          // [nblocks][partitions] each block's open chunks, or null (part_reopen)
     int64_t nchunk = 0;                // chunks in the pool
     int64_t row_cap = 0;               // rows beyond this are counted but not kept
     int shift = 0;                     // partition = key >> shift
@@ -95,9 +96,11 @@ void chunks_reserve(Arena& a, Chunks<KT, V>& c, int64_t row_cap, int nblocks, in
 }
 
 // ------------------------------------------------------------------ one tile
-template <class V>
+// A tile is the work of a block of PART_BLOCK threads, or of more threads with
+// fewer items each.
+template <class V, int BLOCK = PART_BLOCK>
 struct PartSmem {
-    static constexpr int TILE = PART_BLOCK * PartItems<V>::value;
+    static constexpr int TILE = PART_BLOCK * PartItems<V>::value, ITEMS = TILE / BLOCK;
     V vals[TILE];
     uint32_t keys[TILE];
     uint32_t cnt[PART_MAX];            // rows of the tile per partition
@@ -108,13 +111,13 @@ struct PartSmem {
     uint16_t split[PART_MAX];
     uint16_t end[PART_MAX];            // staged rows from here on are not kept (beyond row_cap)
     uint16_t fill[PART_MAX];           // rows in the open chunk (CHUNK: none open)
-    uint32_t scratch[PART_BLOCK / WAVE];
+    uint32_t scratch[BLOCK / WAVE];
     uint64_t claim;
 };
 
-template <class KT, class V>
-__device__ __forceinline__ void part_init(PartSmem<V>& sm) {
-    for (int d = threadIdx.x; d < PART_MAX; d += PART_BLOCK) {
+template <class KT, class V, int BLOCK>
+__device__ __forceinline__ void part_init(PartSmem<V, BLOCK>& sm) {
+    for (int d = threadIdx.x; d < PART_MAX; d += BLOCK) {
         sm.fill[d] = CHUNK;
         sm.cur[d] = 0;
     }
@@ -122,11 +125,11 @@ __device__ __forceinline__ void part_init(PartSmem<V>& sm) {
 
 // Moves the block's tile (the items of each thread whose key is not PART_NONE)
 // into the chunk list.  Called by the whole block.
-template <class KT, class V>
+template <class KT, class V, int BLOCK>
 __device__ __forceinline__ void part_tile_rows(const Chunks<KT, V>& out, int parts,
-                                               const uint32_t (&key)[PartItems<V>::value],
-                                               const V (&val)[PartItems<V>::value], PartSmem<V>& sm) {
-    constexpr int ITEMS = PartItems<V>::value;
+                                               const uint32_t (&key)[PartSmem<V, BLOCK>::ITEMS],
+                                               const V (&val)[PartSmem<V, BLOCK>::ITEMS], PartSmem<V, BLOCK>& sm) {
+    constexpr int ITEMS = PartSmem<V, BLOCK>::ITEMS;
     int tid = threadIdx.x, shift = out.shift;
     // opaque, so that what follows from them is not kept in registers from
     // one tile to the next (143 VGPRs: one block per CU instead of two)
@@ -148,7 +151,7 @@ __device__ __forceinline__ void part_tile_rows(const Chunks<KT, V>& out, int par
         need = c > room ? (c - room + CHUNK - 1) / CHUNK : 0;
     }
     uint32_t tot;
-    const uint32_t excl = block_excl_sum<PART_BLOCK>((need << 16) | c, sm.scratch, &tot);
+    const uint32_t excl = block_excl_sum<BLOCK>((need << 16) | c, sm.scratch, &tot);
     const uint32_t total = tot & 0xFFFFu;
     uint64_t claim = 0;                // in flight while the tile is staged
     if (tid == 0)
@@ -210,7 +213,7 @@ __device__ __forceinline__ void part_tile_rows(const Chunks<KT, V>& out, int par
     }
     // consecutive staged rows of one partition go to consecutive addresses
 #pragma unroll 4
-    for (uint32_t p = tid; p < total; p += PART_BLOCK) {
+    for (uint32_t p = tid; p < total; p += BLOCK) {
         const uint32_t k = sm.keys[p];
         const uint32_t d = k >> shift;
         if (p < sm.end[d]) {
@@ -221,11 +224,25 @@ __device__ __forceinline__ void part_tile_rows(const Chunks<KT, V>& out, int par
     }
 }
 
-// Row counts of the chunks the block leaves part-filled.
-template <class KT, class V>
-__device__ __forceinline__ void part_finish(const Chunks<KT, V>& out, int parts, PartSmem<V>& sm) {
+// Row counts of the chunks the block leaves part-filled, and where they are.
+template <class KT, class V, int BLOCK>
+__device__ __forceinline__ void part_finish(const Chunks<KT, V>& out, int parts, PartSmem<V, BLOCK>& sm) {
     const int d = threadIdx.x;
-    if (d < parts && sm.fill[d] < CHUNK) out.rows[sm.cur[d]] = sm.fill[d];
+    if (d >= parts) return;
+    if (sm.fill[d] < CHUNK) out.rows[sm.cur[d]] = sm.fill[d];
+    if (out.open) out.open[(int64_t)blockIdx.x * parts + d] = sm.fill[d] < CHUNK ? sm.cur[d] : ~0u;
+}
+
+// In place of part_init, a later kernel's block: it goes on filling the chunks
+// that the block of its number left open, so that the kernel adds no
+// part-filled chunks.
+template <class KT, class V, int BLOCK>
+__device__ __forceinline__ void part_reopen(const Chunks<KT, V>& out, int parts, PartSmem<V, BLOCK>& sm) {
+    for (int d = threadIdx.x; d < PART_MAX; d += BLOCK) {
+        const uint32_t c = d < parts ? out.open[(int64_t)blockIdx.x * parts + d] : ~0u;
+        sm.cur[d] = c != ~0u ? c : 0;
+        sm.fill[d] = c != ~0u ? (uint16_t)out.rows[c] : CHUNK;
+    }
 }
 
 // ------------------------------------------------------------------ the lists
@@ -293,7 +310,7 @@ k_part(Src src, Chunks<KT, V> out, int parts, uint32_t key_mask, uint32_t* flags
     constexpr int ITEMS = PartItems<V>::value, TILE = PART_BLOCK * ITEMS;
     __shared__ PartSmem<V> sm;
     const int tid = threadIdx.x, w = wave_index(), l = lane_id();
-    part_init<KT, V>(sm);
+    part_init<KT, V, PART_BLOCK>(sm);
     const int64_t n = src.size();
     const int64_t ntiles = (n + TILE - 1) / TILE;
     uint32_t bad = 0, bad_key = 0;
@@ -301,9 +318,9 @@ k_part(Src src, Chunks<KT, V> out, int parts, uint32_t key_mask, uint32_t* flags
         uint32_t key[ITEMS];
         V val[ITEMS];
         part_load(src, n, tile * TILE + (int64_t)w * ITEMS * WAVE, key, val, key_mask, bad, bad_key);
-        part_tile_rows<KT, V>(out, parts, key, val, sm);
+        part_tile_rows<KT, V, PART_BLOCK>(out, parts, key, val, sm);
     }
-    part_finish<KT, V>(out, parts, sm);
+    part_finish<KT, V, PART_BLOCK>(out, parts, sm);
     if (__any(bad_key != 0) && l == 0) set_flag(flags, FLAG_KEY_RANGE);
     if (__any(bad != 0) && l == 0) set_flag(flags, FLAG_VALUE_RANGE);
 }

@@ -281,7 +281,7 @@ struct SortedRows {
 };
 
 // Rows in the chunk list of a group partition (V: the value's bits).  A wave
-// takes a group of chunks at a time, four of them in flight; when they hold few rows
+// takes a group of chunks at a time, eight of them in flight; when they hold few rows
 // (a small input spread over many blocks), their rows laid end to end, so that
 // the lanes are full and all loads in flight.  finish: the rows claimed (a
 // join's size) go to *d_rows, more than the list keeps raise the capacity
@@ -293,7 +293,7 @@ struct ChunkRows {
     int64_t* d_rows;                               // nullable
     template <int BLOCK, class F>
     __device__ __forceinline__ void each(int64_t b, int, int64_t*, F f) const {
-        constexpr int G = CHUNK_GROUP, PER = CHUNK / WAVE, U = 8;     // loads in flight per thread
+        constexpr int G = CHUNK_GROUP, PER = CHUNK / WAVE, U = 16;    // loads in flight per thread
         constexpr uint32_t SPARSE = U * WAVE;      // rows of a group that one round of loads covers
         const int w = threadIdx.x / WAVE, l = lane_id();
         const uint32_t nc = c.dcount[b];
@@ -389,11 +389,6 @@ k_bucket_agg(Rows rows, int lowb, int64_t nbuckets, uint64_t* status, uint32_t* 
             atomicMin(reinterpret_cast<long long*>(&s_sum[kk]), (long long)v);
         } else if constexpr (OP == BUCKET_MAX) {
             atomicMax(reinterpret_cast<long long*>(&s_sum[kk]), (long long)v);
-        } else if constexpr (std::is_same<VT, uint32_t>::value) {
-            // 32-bit add on the low word; a wrap carries into the high word
-            uint32_t* w2 = reinterpret_cast<uint32_t*>(&s_sum[kk]);
-            const uint32_t old = atomicAdd(&w2[0], v);
-            if (old + v < old) atomicAdd(&w2[1], 1u);
         } else {
             atomicAdd(&s_sum[kk], (unsigned long long)v);
         }

@@ -101,13 +101,14 @@ void table_join_reserve(Arena& a, const tqp_ctx* ctx, TableJoin<V>& j, int64_t n
         probe_blocks = grid_for(j.fact.nchunk + (int64_t(1) << j.fact_bits) * probe_chunks<V>(), probe_chunks<V>(),
                                 (int64_t)ctx->num_cus * PART_BLOCKS_PER_CU);
     if (j.fact_bits) probe_blocks = (probe_blocks + XCDS - 1) / XCDS * XCDS;
-    // k_probe_lists: its LDS leaves one block per CU
-    j.dup_blocks = std::min(probe_blocks, spread > 1 ? ctx->num_cus : ctx->num_cus / 4);
+    // k_probe_lists: its LDS leaves one block per CU, and its blocks go on with
+    // the chunks of the probe's
+    j.dup_blocks = std::min(probe_blocks, ctx->num_cus);
     int pb = part_bits_for(spread * join_cap, probe_blocks, PART_MAX_BITS);
     pb = std::min(cb, std::max(pb, cb - BUCKET_LOWB_MAX));
     j.lowb = cb - pb;
-    chunks_reserve(a, j.grp, join_cap, probe_blocks + j.dup_blocks, cb, pb);
-    j.grp.nblocks = probe_blocks;
+    chunks_reserve(a, j.grp, join_cap, probe_blocks, cb, pb);
+    j.grp.open = a.scratch<uint32_t>((int64_t)probe_blocks << pb);
     j.spill.at = a.scratch<uint32_t>(n_fact);
     j.spill.n = a.zero<unsigned long long>(1);
 }
@@ -116,8 +117,8 @@ void table_join_reserve(Arena& a, const tqp_ctx* ctx, TableJoin<V>& j, int64_t n
 // One block per slice.  SORTED: the dim rows are n rows sorted by key, those
 // of the slice one range; else the chunk list of the slice's partition, whose
 // other slices' rows are skipped.  Bound by latency and by the slices' turns
-// (one block of 128 KB LDS per CU, 2^26 keys in 2048 slices): 161 us for 15M
-// rows and 256 MB of table, 2.3 TB/s; slices of 2^14 keys read every partition
+// (one block of 128 KB LDS per CU, 2^26 keys in 2048 slices): 147 us for 15M
+// rows and 256 MB of table (every slice reads its partition, eight slices, from L2); slices of 2^14 keys read every partition
 // twice as often and are slower.
 constexpr int TJ_BUILD_BLOCK = 1024;
 template <bool SORTED>
@@ -130,7 +131,6 @@ k_table_build(JoinTable t, const uint32_t* dkey, const uint32_t* dval, int64_t n
     __shared__ uint32_t s_scan[W];
     const int tid = threadIdx.x, w = tid / WAVE, l = lane_id();
     const uint32_t k0 = blockIdx.x << t.slice_bits, keys = 1u << t.slice_bits;
-    const int per = (keys + TJ_BUILD_BLOCK - 1) / TJ_BUILD_BLOCK;             // slots per thread
     const int part = (int)(k0 >> (t.key_bits - t.part_bits));
     if (SORTED) {
         if (w < 2) {
@@ -171,16 +171,19 @@ k_table_build(JoinTable t, const uint32_t* dkey, const uint32_t* dval, int64_t n
                 enter(k, vp, in);
             }
         } else {
-            constexpr uint32_t G = CHUNK_GROUP;
+            // an even share of the partition's chunks per wave
+            constexpr uint32_t C = U / PER;
             const uint32_t nc = t.rows.dcount[part];
             const uint32_t* dir = t.rows.list + t.rows.first[part];
-            for (uint32_t c0 = w * G; c0 < nc; c0 += W * G) {
+            const uint32_t share = ((nc + W - 1) / W + C - 1) / C * C;
+            const uint32_t end = (w + 1) * share < nc ? (w + 1) * share : nc;
+            for (uint32_t c0 = w * share; c0 < end; c0 += WAVE) {
                 uint32_t id = 0, rows = 0;
-                if (l < (int)G && c0 + l < nc) {
+                if (c0 + l < end) {
                     id = dir[c0 + l];
                     rows = t.rows.rows[id];
                 }
-                for (uint32_t g = 0; g < G && c0 + g < nc; g += U / PER) {
+                for (uint32_t g = 0; g < (uint32_t)WAVE && c0 + g < end; g += C) {
 #pragma unroll
                     for (int q = 0; q < U; ++q) {     // rows past the end read the chunk's first row
                         const int64_t at = (int64_t)wave_read(id, g + q / PER) * CHUNK;
@@ -208,8 +211,7 @@ k_table_build(JoinTable t, const uint32_t* dkey, const uint32_t* dval, int64_t n
         each([&](uint32_t k, uint32_t) { atomicAdd(&s_slot[k], 1u); });
         __syncthreads();
         uint32_t mine = 0;
-        const uint32_t i0 = tid * per, i1 = i0 + per < keys ? i0 + per : keys;
-        for (uint32_t i = i0; i < i1; ++i) mine += s_slot[i] > 1 ? s_slot[i] + 1 : 0;
+        for (uint32_t i = tid; i < keys; i += TJ_BUILD_BLOCK) mine += s_slot[i] > 1 ? s_slot[i] + 1 : 0;
         uint32_t tot;
         uint32_t off = block_excl_sum<TJ_BUILD_BLOCK>(mine, s_scan, &tot);
         if (tid == 0) s_base = atomicAdd(t.list_n, tot);
@@ -217,7 +219,7 @@ k_table_build(JoinTable t, const uint32_t* dkey, const uint32_t* dval, int64_t n
         off += s_base;
         // a list is filled from its end: the slot counts down to the place
         // after its number of entries
-        for (uint32_t i = i0; i < i1; ++i) {
+        for (uint32_t i = tid; i < keys; i += TJ_BUILD_BLOCK) {
             const uint32_t c = s_slot[i];
             if (c > 1) {
                 t.list[off] = c;
@@ -309,7 +311,7 @@ k_probe_cols(Src src, JoinTable t, Spill sp, Chunks<uint16_t, V> out, int parts,
     constexpr int ITEMS = PartItems<V>::value, TILE = PART_BLOCK * ITEMS;
     __shared__ PartSmem<V> sm;
     const int w = wave_index(), l = lane_id();
-    part_init<uint16_t, V>(sm);
+    part_init<uint16_t, V, PART_BLOCK>(sm);
     const int64_t n = src.size();
     const int64_t ntiles = (n + TILE - 1) / TILE;
     const uint32_t key_mask = (uint32_t)((uint64_t(1) << t.key_bits) - 1);
@@ -321,9 +323,9 @@ k_probe_cols(Src src, JoinTable t, Spill sp, Chunks<uint16_t, V> out, int parts,
         const int64_t base = tile * TILE + (int64_t)w * ITEMS * WAVE;
         part_load(src, n, base, key, val, key_mask, bad, bad_key);
         probe_rows<V>(t, sp, key, [&](int j) { return (uint32_t)(base + j * WAVE + l); }, wide);
-        part_tile_rows<uint16_t, V>(out, parts, key, val, sm);
+        part_tile_rows<uint16_t, V, PART_BLOCK>(out, parts, key, val, sm);
     }
-    part_finish<uint16_t, V>(out, parts, sm);
+    part_finish<uint16_t, V, PART_BLOCK>(out, parts, sm);
     if (__any(bad_key != 0 || wide) && l == 0) set_flag(flags, FLAG_KEY_RANGE);
     if (__any(bad != 0) && l == 0) set_flag(flags, FLAG_VALUE_RANGE);
 }
@@ -347,7 +349,7 @@ k_probe_chunks(Chunks<uint32_t, V> fact, int fact_parts, JoinTable t, Spill sp, 
     __shared__ PartSmem<V> sm;
     __shared__ uint32_t s_item[PART_MAX + 1];         // first item of each partition
     const int tid = threadIdx.x, w = wave_index(), l = lane_id();
-    part_init<uint16_t, V>(sm);
+    part_init<uint16_t, V, PART_BLOCK>(sm);
     {
         const uint32_t nc = tid < fact_parts ? fact.dcount[tid] : 0;
         uint32_t tot;
@@ -400,9 +402,9 @@ k_probe_chunks(Chunks<uint32_t, V> fact, int fact_parts, JoinTable t, Spill sp, 
         for (int q = 0; q < CPW; ++q) at[q] = id[q];
         if (it + per_xcd < i1) find(it + per_xcd);
         probe_rows<V>(t, sp, key, [&](int j) { return at[j / PER] * CHUNK + (j % PER) * WAVE + ll; }, wide);
-        part_tile_rows<uint16_t, V>(out, parts, key, val, sm);
+        part_tile_rows<uint16_t, V, PART_BLOCK>(out, parts, key, val, sm);
     }
-    part_finish<uint16_t, V>(out, parts, sm);
+    part_finish<uint16_t, V, PART_BLOCK>(out, parts, sm);
     if (__any(wide) && l == 0) set_flag(flags, FLAG_KEY_RANGE);
 }
 
@@ -433,20 +435,21 @@ struct PlaceChunks {
     __device__ uint32_t key(uint32_t at) const { return keys[at]; }
     __device__ V value(uint32_t at) const { return vals[at]; }
 };
+constexpr int LISTS_BLOCK = 1024;      // its LDS leaves one block per CU
 template <class V, class Place>
-__global__ void __launch_bounds__(PART_BLOCK)
+__global__ void __launch_bounds__(LISTS_BLOCK)
 k_probe_lists(Place place, JoinTable t, Spill sp, Chunks<uint16_t, V> out, int parts, uint32_t* flags) {
-    constexpr int ITEMS = PartItems<V>::value, TILE = PART_BLOCK * ITEMS;
-    constexpr int ROWS = sizeof(V) <= 4 ? 4096 : 2048, PER = ROWS / PART_BLOCK;
-    __shared__ PartSmem<V> sm;
+    constexpr int ITEMS = PartSmem<V, LISTS_BLOCK>::ITEMS, TILE = LISTS_BLOCK * ITEMS;
+    constexpr int ROWS = sizeof(V) <= 4 ? 4096 : 2048, PER = ROWS / LISTS_BLOCK;
+    __shared__ PartSmem<V, LISTS_BLOCK> sm;
     __shared__ int64_t s_first[ROWS];         // first place of each row's list
     __shared__ uint32_t s_list[ROWS];
     __shared__ V s_val[ROWS];
-    __shared__ int64_t s_scan[PART_BLOCK / WAVE];
+    __shared__ int64_t s_scan[LISTS_BLOCK / WAVE];
     const int tid = threadIdx.x, w = wave_index(), l = lane_id();
     const int64_t n = (int64_t)*sp.n;
     if ((int64_t)blockIdx.x * ROWS >= n) return;
-    part_init<uint16_t, V>(sm);
+    part_reopen<uint16_t, V, LISTS_BLOCK>(out, parts, sm);
     bool wide = false;
     for (int64_t r0 = (int64_t)blockIdx.x * ROWS; r0 < n; r0 += (int64_t)gridDim.x * ROWS) {
         __syncthreads();                              // the previous rows are expanded
@@ -458,10 +461,14 @@ k_probe_lists(Place place, JoinTable t, Spill sp, Chunks<uint16_t, V> out, int p
             const uint32_t list = t.slot[place.key(at)] & ~TJ_LIST;
             s_list[tid * PER + q] = list;
             s_val[tid * PER + q] = place.value(at);
-            len[q] = r < n ? (int64_t)t.list[list] : 0;
+            len[q] = t.list[list];
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            if (r0 + tid * PER + q >= n) len[q] = 0;
             mine += len[q];
         }
-        int64_t total, at = block_excl_sum<PART_BLOCK>(mine, s_scan, &total);
+        int64_t total, at = block_excl_sum<LISTS_BLOCK>(mine, s_scan, &total);
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             s_first[tid * PER + q] = at;
@@ -474,20 +481,21 @@ k_probe_lists(Place place, JoinTable t, Spill sp, Chunks<uint16_t, V> out, int p
 #pragma unroll
             for (int j = 0; j < ITEMS; ++j) {
                 const int64_t q = q0 + (int64_t)w * ITEMS * WAVE + j * WAVE + l;
-                int lo = 0, hi = ROWS;        // last row whose list starts at or before q
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (s_first[mid] <= q) lo = mid; else hi = mid;
-                }
-                const uint32_t e = q < total ? t.list[s_list[lo] + 1 + (uint32_t)(q - s_first[lo])] : 0u;
+                const int64_t qc = q < total ? q : total - 1;
+                int lo = 0;                   // last row whose list starts at or before q
+#pragma unroll
+                for (int step = ROWS / 2; step; step /= 2)
+                    if (s_first[lo + step] <= qc) lo += step;
+                uint32_t e = t.list[s_list[lo] + 1 + (uint32_t)(qc - s_first[lo])];
+                if (q >= total) e = 0;
                 wide |= (e & TJ_WIDE) != 0;
                 key[j] = (e & ~TJ_WIDE) - 1;          // past the end: PART_NONE
                 val[j] = s_val[lo];
             }
-            part_tile_rows<uint16_t, V>(out, parts, key, val, sm);
+            part_tile_rows<uint16_t, V, LISTS_BLOCK>(out, parts, key, val, sm);
         }
     }
-    part_finish<uint16_t, V>(out, parts, sm);
+    part_finish<uint16_t, V, LISTS_BLOCK>(out, parts, sm);
     if (__any(wide) && l == 0) set_flag(flags, FLAG_KEY_RANGE);
 }
 
@@ -512,7 +520,7 @@ tqp_status table_probe(tqp_ctx* ctx, hipStream_t s, const TableJoin<V>& j, const
                            j.fact, 1 << j.fact_bits, j.t, j.spill, j.grp, parts, ctx->d_err)));
             using Place = PlaceChunks<V>;
             TQP_LAUNCH(ctx, s, lists_name,
-                       (k_probe_lists<V, Place><<<(unsigned)j.dup_blocks, PART_BLOCK, 0, s>>>(
+                       (k_probe_lists<V, Place><<<(unsigned)j.dup_blocks, LISTS_BLOCK, 0, s>>>(
                            Place{j.fact.keys, j.fact.vals}, j.t, j.spill, j.grp, parts, ctx->d_err)));
         } else {
             TQP_LAUNCH(ctx, s, name,
@@ -520,7 +528,7 @@ tqp_status table_probe(tqp_ctx* ctx, hipStream_t s, const TableJoin<V>& j, const
                            src, j.t, j.spill, j.grp, parts, ctx->d_err)));
             using Place = PlaceCols<V, Src>;
             TQP_LAUNCH(ctx, s, lists_name,
-                       (k_probe_lists<V, Place><<<(unsigned)j.dup_blocks, PART_BLOCK, 0, s>>>(
+                       (k_probe_lists<V, Place><<<(unsigned)j.dup_blocks, LISTS_BLOCK, 0, s>>>(
                            Place{src}, j.t, j.spill, j.grp, parts, ctx->d_err)));
         }
     }
