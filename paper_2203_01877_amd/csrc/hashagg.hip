@@ -23,7 +23,8 @@
 // load.
 //
 // Few groups (a table of 2 * gcap slots fits in 64 KB of LDS, 128 KB with
-// distinct counts: gcap <= 2048 for sum and count, 1024 with everything):
+// distinct counts or many rows: gcap <= 2048 or 4096 for sum and count, 1024
+// or 2048 with min and max):
 // each block first aggregates its rows in a table in LDS and merges its
 // groups into the global table at the end, so the global atomics per block
 // are one per group, not one per row.
@@ -49,6 +50,8 @@
 //
 // Output: one row per group in no fixed order (slot order, compacted by wave
 // ballots), the group count in *d_ngroups.
+#include <cmath>
+
 #include "dev.hpp"
 #include "host.hpp"
 #include "radix.hpp"
@@ -57,12 +60,18 @@ namespace tqp {
 namespace {
 
 constexpr int HA_BLOCK = 256;
+constexpr int HA_LOCAL_BLOCK = 1024;        // threads that share a per-block table
+constexpr int HA_MERGE_STEP = 67;
 constexpr int HA_ITEMS = 4;                 // rows per thread per step, probed in lockstep
 constexpr int HA_LDS_MIN = 256;             // slots of the per-block table: 2 * gcap (or 4 * gcap), at least this
 constexpr int HA_LDS_BYTES = 65536;         // LDS of a partition's table
-// LDS of the per-block table: 64 KB, or 128 KB (of the 160 KB of a CU) with
-// distinct counts, which have no partitioned path to fall back on
-constexpr int ha_local_bytes(bool dist) { return dist ? 131072 : 65536; }
+// LDS of the per-block table (of the 160 KB of a CU): 128 KB with distinct
+// counts, which have no partitioned path to fall back on, and for many rows;
+// 64 KB else.  MIN and MAX too over 2000 groups, where the table takes 128 KB:
+// 177 us for 30M rows and 92 for 6M where the partitioned path takes 488 and
+// 113, but 58 against 50 for 1M.
+constexpr int64_t HA_MANY_ROWS = int64_t(1) << 21;
+constexpr int ha_local_bytes(bool dist, int64_t n) { return dist || n >= HA_MANY_ROWS ? 131072 : 65536; }
 constexpr uint32_t HA_PROBE_LIMIT = 4096;
 constexpr unsigned long long ORD_BIAS = 1ull << 63;
 
@@ -211,22 +220,33 @@ __device__ __forceinline__ void ha_distinct(const HaArgs& a, const uint32_t (&k1
         if (live[j]) set_flag(a.flags, FLAG_CAPACITY);
 }
 
-// Loads ITEMS rows: row r of step `base` is base + j * HA_BLOCK + tid, so each
-// item's loads are coalesced across the block.
-template <bool VAL, bool DIST>
-__device__ __forceinline__ void ha_load(const HaArgs& a, int64_t n, int64_t base, uint32_t (&k1)[HA_ITEMS],
-                                        bool (&in)[HA_ITEMS], int64_t (&v)[HA_ITEMS], int32_t (&d)[HA_ITEMS]) {
+// Loads ITEMS rows: row r of step `base` is base + j * BLOCK + tid, so each
+// item's loads are coalesced across the block.  base < n; rows past the end
+// read the last one, so that no branch lies between the loads.
+template <bool VAL, bool DIST, int BLOCK>
+__device__ __forceinline__ void ha_load(const HaArgs& a, int64_t n, int64_t base, int32_t (&k)[HA_ITEMS],
+                                        int64_t (&v)[HA_ITEMS], int32_t (&d)[HA_ITEMS]) {
 #pragma unroll
     for (int j = 0; j < HA_ITEMS; ++j) {
-        const int64_t i = base + (int64_t)j * HA_BLOCK + threadIdx.x;
-        const bool ok = i < n;
-        const int32_t k = ok ? a.gkey[i] : 0;
-        if (ok && k < 0) set_flag(a.flags, FLAG_KEY_RANGE);
-        in[j] = ok && k >= 0;
-        k1[j] = (uint32_t)k + 1u;
-        v[j] = VAL && ok ? a.val[i] : 0;
-        d[j] = DIST && ok ? a.dval[i] : 0;
+        const int64_t i = base + (int64_t)j * BLOCK + threadIdx.x;
+        const int64_t ic = i < n ? i : n - 1;
+        k[j] = a.gkey[ic];
+        v[j] = VAL ? a.val[ic] : 0;
+        d[j] = DIST ? a.dval[ic] : 0;
     }
+}
+template <int BLOCK>
+__device__ __forceinline__ void ha_keys(const HaArgs& a, int64_t n, int64_t base, const int32_t (&k)[HA_ITEMS],
+                                        uint32_t (&k1)[HA_ITEMS], bool (&in)[HA_ITEMS]) {
+    bool bad = false;
+#pragma unroll
+    for (int j = 0; j < HA_ITEMS; ++j) {
+        const bool ok = base + (int64_t)j * BLOCK + threadIdx.x < n;
+        bad |= ok && k[j] < 0;
+        in[j] = ok && k[j] >= 0;
+        k1[j] = (uint32_t)k[j] + 1u;
+    }
+    if (bad) set_flag(a.flags, FLAG_KEY_RANGE);
 }
 
 template <bool VAL, bool MINMAX>
@@ -246,11 +266,12 @@ __global__ void __launch_bounds__(HA_BLOCK) k_ha_global(HaArgs a) {
     const int64_t n = ha_rows(a);
     const int64_t step = (int64_t)gridDim.x * HA_BLOCK * HA_ITEMS;
     for (int64_t base = (int64_t)blockIdx.x * HA_BLOCK * HA_ITEMS; base < n; base += step) {
+        int32_t k[HA_ITEMS], d[HA_ITEMS];
+        int64_t v[HA_ITEMS];
         uint32_t k1[HA_ITEMS];
         bool in[HA_ITEMS];
-        int64_t v[HA_ITEMS];
-        int32_t d[HA_ITEMS];
-        ha_load<VAL, DIST>(a, n, base, k1, in, v, d);
+        ha_load<VAL, DIST, HA_BLOCK>(a, n, base, k, v, d);
+        ha_keys<HA_BLOCK>(a, n, base, k, k1, in);
         int32_t slot[HA_ITEMS];
         ha_find(a, k1, in, slot);
 #pragma unroll
@@ -269,9 +290,12 @@ __global__ void __launch_bounds__(HA_BLOCK) k_ha_global(HaArgs a) {
 }
 
 // Few groups: a per-block LDS table first, merged into the global table at
-// the end.  A row whose LDS probe fails (more groups than the LDS table
-// holds, which only an input with more than gcap groups reaches) goes to the
-// global table directly.
+// the end.  A block of 1024 threads per CU, with the next rows in flight and
+// the first slots of all items read at once: bound by the latency of LDS and,
+// with many groups, by the merges' global atomics (30M rows, 1000 groups, every
+// statistic: 411 us with 256 threads per table, 130 so).  A row whose LDS
+// probe fails (more groups than the LDS table holds, which only an input with
+// more than gcap groups reaches) goes to the global table directly.
 template <bool VAL, bool MINMAX, bool DIST>
 constexpr int ha_lds_slot_bytes() {
     return 8 + (VAL ? 8 : 0) + (MINMAX ? 16 : 0) + (DIST ? 4 : 0);
@@ -292,7 +316,7 @@ constexpr int HA_LSET_PROBE = 16;
 constexpr int64_t HA_LSET_GROUPS = 64;
 
 template <bool VAL, bool MINMAX, bool DIST>
-__global__ void __launch_bounds__(HA_BLOCK) k_ha_local(HaArgs a, int lg, int pset) {
+__global__ void __launch_bounds__(HA_LOCAL_BLOCK) k_ha_local(HaArgs a, int lg, int pset) {
     extern __shared__ __align__(16) unsigned long long ha_smem[];
     const int S = 1 << lg;
     unsigned long long* s_pset = ha_smem;
@@ -302,7 +326,7 @@ __global__ void __launch_bounds__(HA_BLOCK) k_ha_local(HaArgs a, int lg, int pse
     uint32_t* s_key = reinterpret_cast<uint32_t*>(s_nmin + (MINMAX ? S : 0));
     uint32_t* s_cnt = s_key + S;
     uint32_t* s_nd = s_cnt + S;
-    for (int i = threadIdx.x; i < S; i += HA_BLOCK) {
+    for (int i = threadIdx.x; i < S; i += HA_LOCAL_BLOCK) {
         s_key[i] = 0u;
         s_cnt[i] = 0u;
         if (VAL) s_sum[i] = 0ull;
@@ -310,16 +334,29 @@ __global__ void __launch_bounds__(HA_BLOCK) k_ha_local(HaArgs a, int lg, int pse
         if (DIST) s_nd[i] = 0u;
     }
     if (DIST && pset)
-        for (int i = threadIdx.x; i < HA_LSET; i += HA_BLOCK) s_pset[i] = 0ull;
+        for (int i = threadIdx.x; i < HA_LSET; i += HA_LOCAL_BLOCK) s_pset[i] = 0ull;
     __syncthreads();
     const int64_t n = ha_rows(a);
-    const int64_t step = (int64_t)gridDim.x * HA_BLOCK * HA_ITEMS;
-    for (int64_t base = (int64_t)blockIdx.x * HA_BLOCK * HA_ITEMS; base < n; base += step) {
+    const int64_t step = (int64_t)gridDim.x * HA_LOCAL_BLOCK * HA_ITEMS;
+    int32_t nk[HA_ITEMS], nd[HA_ITEMS];             // the next step's rows
+    int64_t nv[HA_ITEMS];
+    if ((int64_t)blockIdx.x * HA_LOCAL_BLOCK * HA_ITEMS < n)
+        ha_load<VAL, DIST, HA_LOCAL_BLOCK>(a, n, (int64_t)blockIdx.x * HA_LOCAL_BLOCK * HA_ITEMS, nk, nv, nd);
+    for (int64_t base = (int64_t)blockIdx.x * HA_LOCAL_BLOCK * HA_ITEMS; base < n; base += step) {
         uint32_t k1[HA_ITEMS];
         bool in[HA_ITEMS];
         int64_t v[HA_ITEMS];
         int32_t d[HA_ITEMS];
-        ha_load<VAL, DIST>(a, n, base, k1, in, v, d);
+        ha_keys<HA_LOCAL_BLOCK>(a, n, base, nk, k1, in);
+#pragma unroll
+        for (int j = 0; j < HA_ITEMS; ++j) v[j] = nv[j], d[j] = nd[j];
+        if (base + step < n) ha_load<VAL, DIST, HA_LOCAL_BLOCK>(a, n, base + step, nk, nv, nd);     // in flight meanwhile
+        uint32_t home[HA_ITEMS], key0[HA_ITEMS];
+#pragma unroll
+        for (int j = 0; j < HA_ITEMS; ++j) {
+            home[j] = ha_home(k1[j], lg);
+            key0[j] = s_key[home[j]];
+        }
         int32_t ls[HA_ITEMS];
         bool spill[HA_ITEMS];
 #pragma unroll
@@ -327,9 +364,9 @@ __global__ void __launch_bounds__(HA_BLOCK) k_ha_local(HaArgs a, int lg, int pse
             ls[j] = -1;
             spill[j] = false;
             if (!in[j]) continue;
-            uint32_t s = ha_home(k1[j], lg);
+            uint32_t s = home[j];
             for (int p = 0; p < S; ++p) {
-                uint32_t cur = s_key[s];
+                uint32_t cur = p ? s_key[s] : key0[j];
                 if (cur == 0u) cur = atomicCAS(&s_key[s], 0u, k1[j]);
                 if (cur == 0u || cur == k1[j]) { ls[j] = (int32_t)s; break; }
                 s = (s + 1) & (S - 1);
@@ -386,9 +423,10 @@ __global__ void __launch_bounds__(HA_BLOCK) k_ha_local(HaArgs a, int lg, int pse
         }
     }
     __syncthreads();
-    // merge this block's groups
-    for (int i0 = 0; i0 < S; i0 += HA_BLOCK) {
-        const int i = i0 + threadIdx.x;
+    // merge this block's groups, each block from another slot on, so that the
+    // blocks do not meet at the same groups
+    for (int i0 = threadIdx.x; i0 < S; i0 += HA_LOCAL_BLOCK) {
+        const int i = (i0 + (int)blockIdx.x * HA_MERGE_STEP) & (S - 1);
         uint32_t k1[1] = {s_key[i]};
         bool in[1] = {k1[0] != 0u};
         int32_t gs[1];
@@ -877,18 +915,29 @@ void hp_plan(int64_t gcap, int& P, int& lg) {
 // log2 of the LDS table's slots for gcap groups, or -1 when it would not fit
 // (the global table then takes every row).
 template <bool VAL, bool MINMAX, bool DIST>
-int ha_lds_log2(int64_t gcap) {
+int ha_lds_log2(int64_t gcap, int64_t n) {
     int lg = 0;
     while ((int64_t(1) << lg) < 2 * gcap || (1 << lg) < HA_LDS_MIN) ++lg;
     const int64_t set = DIST && gcap <= HA_LSET_GROUPS ? HA_LSET * 8 : 0;
     // A table sized by the group bound (not by its minimum) gets twice the
     // slots when they fit: at a quarter full its linear probes stay short,
     // and a wave waits for its longest (SUM and COUNT over 1000 groups:
-    // 0.63 -> 0.54 ms for 60M rows).  A minimum-size table keeps its size:
-    // doubling it only adds clearing and merging.
+    // 0.63 -> 0.54 ms for 60M rows by blocks of 256), up to 64 KB (1500 groups,
+    // 30M rows: 123 us in 64 KB, 128 in 128 KB; 1M rows 40 and 51).  A
+    // minimum-size table keeps its size: doubling it only adds clearing and
+    // merging.
     const int64_t bytes = ha_lds_slot_bytes<VAL, MINMAX, DIST>();
-    if ((int64_t(1) << lg) > HA_LDS_MIN && (int64_t(1) << (lg + 1)) * bytes + set <= ha_local_bytes(DIST)) return lg + 1;
-    return ((int64_t(1) << lg) * bytes + set <= ha_local_bytes(DIST)) ? lg : -1;
+    if ((int64_t(1) << lg) > HA_LDS_MIN && (int64_t(1) << (lg + 1)) * bytes + set <= ha_local_bytes(DIST, 0)) return lg + 1;
+    return ((int64_t(1) << lg) * bytes + set <= ha_local_bytes(DIST, n)) ? lg : -1;
+}
+
+// Blocks of the local kernel, at most one per CU: the rows' work falls with
+// their number, that of the merges (blocks * groups) rises with it.  30M rows
+// take 55 us of row work in 256 blocks, merging 1000 groups of every block 85:
+// both are the same in 1.2 * sqrt(n / gcap) blocks.
+inline int ha_local_blocks(const tqp_ctx* ctx, int64_t n, int64_t gcap) {
+    const int64_t even = (int64_t)(1.2 * std::sqrt((double)n / (double)(gcap < 1 ? 1 : gcap))) + 1;
+    return grid_for(n, (int64_t)HA_LOCAL_BLOCK * HA_ITEMS, std::min<int64_t>(even, ctx->num_cus));
 }
 
 template <bool VAL, bool MINMAX, bool DIST>
@@ -900,26 +949,18 @@ tqp_status ha_run(tqp_ctx* ctx, const HaArgs& a, int64_t gcap, int64_t n, hipStr
             b = 4;
         return b < 1 ? 1 : b;
     }();
-    static int per_cu_local[2][32] = {};            // by the pair set's use and log2 of the LDS slots
-    const int lg = ha_lds_log2<VAL, MINMAX, DIST>(gcap);
+    const int lg = ha_lds_log2<VAL, MINMAX, DIST>(gcap, n);
     if (lg >= 0) {
         const int pset = DIST && gcap <= HA_LSET_GROUPS;
         const size_t lds = ((size_t)1 << lg) * ha_lds_slot_bytes<VAL, MINMAX, DIST>() + (pset ? HA_LSET * 8 : 0);
-        int& per_cu = per_cu_local[pset][lg];
-        if (!per_cu) {
-            if (lds > 65536 &&
-                hipFuncSetAttribute(reinterpret_cast<const void*>(k_ha_local<VAL, MINMAX, DIST>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-                return fail(TQP_ERR_HIP, "tqp_hash_groupby: %zu bytes of LDS refused", lds);
-            int b = 1;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_ha_local<VAL, MINMAX, DIST>, HA_BLOCK, lds) !=
-                hipSuccess)
-                b = 1;
-            per_cu = b < 1 ? 1 : b;
-        }
-        const int grid = grid_for(n, (int64_t)HA_BLOCK * HA_ITEMS, (int64_t)ctx->num_cus * per_cu);
+        static const hipError_t allowed =
+            hipFuncSetAttribute(reinterpret_cast<const void*>(k_ha_local<VAL, MINMAX, DIST>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, ha_local_bytes(DIST, HA_MANY_ROWS));
+        if (lds > 65536 && allowed != hipSuccess)
+            return fail(TQP_ERR_HIP, "tqp_hash_groupby: %zu bytes of LDS refused", lds);
         TQP_LAUNCH(ctx, stream, "hashagg_local",
-                   k_ha_local<VAL, MINMAX, DIST><<<grid, HA_BLOCK, lds, stream>>>(a, lg, pset));
+                   k_ha_local<VAL, MINMAX, DIST><<<ha_local_blocks(ctx, n, gcap), HA_LOCAL_BLOCK, lds, stream>>>(
+                       a, lg, pset));
     } else {
         const int grid = grid_for(n, (int64_t)HA_BLOCK * HA_ITEMS, (int64_t)ctx->num_cus * per_cu_global);
         TQP_LAUNCH(ctx, stream, "hashagg_global", k_ha_global<VAL, MINMAX, DIST><<<grid, HA_BLOCK, 0, stream>>>(a));
@@ -952,7 +993,7 @@ tqp_status tqp_hash_groupby(tqp_ctx* ctx, const int32_t* gkey, int64_t n, const 
     const bool want_dist = out_ndist != nullptr;
     // many groups with sum / min / max: partitioned (no global table)
     const bool part = want_val && !want_dist && n > 0 &&
-                      (want_mm ? ha_lds_log2<true, true, false>(gcap) : ha_lds_log2<true, false, false>(gcap)) < 0;
+                      (want_mm ? ha_lds_log2<true, true, false>(gcap, n) : ha_lds_log2<true, false, false>(gcap, n)) < 0;
     if (part) {
         int P = 0, lg = 0;
         if (want_mm) hp_plan<true>(gcap, P, lg);
@@ -998,9 +1039,9 @@ tqp_status tqp_hash_groupby(tqp_ctx* ctx, const int32_t* gkey, int64_t n, const 
     }
     // distinct counts with many groups: partitioned too
     if (want_dist && n > 0) {
-        const int lg_local = want_mm ? ha_lds_log2<true, true, true>(gcap)
-                             : want_val ? ha_lds_log2<true, false, true>(gcap)
-                                        : ha_lds_log2<false, false, true>(gcap);
+        const int lg_local = want_mm ? ha_lds_log2<true, true, true>(gcap, n)
+                             : want_val ? ha_lds_log2<true, false, true>(gcap, n)
+                                        : ha_lds_log2<false, false, true>(gcap, n);
         if (lg_local < 0) {
             HaOut o{out_key, out_cnt, out_sum, out_min, out_max, out_ndist, gcap};
             if (want_mm) return hpd_run<true, true>(ctx, gkey, val, dval, n, d_n, o, gcap, d_ngroups, ws, ws_bytes, stream);
