@@ -45,6 +45,7 @@
 // counts.
 #include "filter.hpp"
 #include "fragment.hpp"
+#include "pairtable.hpp"
 #include "tablejoin.hpp"
 
 namespace tqp {
@@ -584,6 +585,8 @@ struct GenBufs {
     bool table = false;                      // its join by a key table (tablejoin.hpp) instead of the sorts
     TableJoin<uint64_t> tj64;
     TableJoin<uint32_t> tj32;
+    bool pairs = false;                      // the pairs by a key table (pairtable.hpp) instead of the sorts
+    PairTable pt;
     JoinBufs jb;
     uint32_t *fsk = nullptr, *fsv = nullptr, *dsk = nullptr, *dsv = nullptr;
     uint64_t* fstatus = nullptr;             // no join: the compaction of the kept fact rows
@@ -682,6 +685,9 @@ void gen_reserve(Arena& a, const tqp_ctx* ctx, const tqp_fragment& f, const tqp_
         b.kv = b.bucket && b.fpush && b.dpush >= 0 && f.n_group == 1;
         b.v32 = b.kv && f.value_bits == 32;
         b.table = spread && b.kv && table_join_ok(ctx, N, f.n_dim, kb, b.gbits);
+        b.pairs = spread && !b.kv && pair_table_ok(ctx, N, f.n_dim, kb);
+        // every column is read through the pairs then
+        if (b.pairs) b.fpush = false, b.dpush = -1;
     }
     if (f.n_fact_pred > 0) b.fkeep = a.scratch<uint8_t>(N);
     if (b.join && f.n_dim_pred > 0) b.dkeep = a.scratch<uint8_t>(f.n_dim);
@@ -696,6 +702,9 @@ void gen_reserve(Arena& a, const tqp_ctx* ctx, const tqp_fragment& f, const tqp_
             b.lowb = b.tj64.lowb;
         }
         b.nbuckets = int64_t(1) << (b.gbits - b.lowb);
+    } else if (b.pairs) {
+        pair_table_reserve(a, b.pt, f.n_dim, kb, J);
+        b.ri = a.scratch<int32_t>(J);
     } else if (b.join) {
         b.flowb = join_low_bits(N, kb, Cfg::RADIX_BITS, JCfgGen::TILE, JCfgGen::RWIN);
         if (b.flowb > FINISH_LOG2) b.flowb = FINISH_LOG2;
@@ -756,7 +765,7 @@ void gen_reserve(Arena& a, const tqp_ctx* ctx, const tqp_fragment& f, const tqp_
     // rows then come in runs of nearby rows, which the caches serve.  Worth
     // it when those columns outgrow the chip's last-level cache (random
     // reads of a table that fits it are served there).
-    if (b.join && !b.fpush && b.reads_fact && N * b.fact_row_bytes > GF_LORDER_MIN_BYTES) {
+    if (b.join && !b.pairs && !b.fpush && b.reads_fact && N * b.fact_row_bytes > GF_LORDER_MIN_BYTES) {
         int rb = 1;
         while (rb < 31 && (int64_t(1) << rb) < N) ++rb;
         b.lorder = true;
@@ -1061,7 +1070,10 @@ tqp_status gen_launch(tqp_ctx* ctx, const tqp_fragment& f, const tqp_fragment_ou
         return st;
     const uint32_t* rk = b.dsk;
     const uint32_t* rv = b.dsv;
-    if (b.join) {
+    if (b.pairs) {
+        SrcKeepRow ds{static_cast<const int32_t*>(f.dim_cols[f.dim_key].data), b.dkeep, f.n_dim};
+        if ((st = pair_build(ctx, sd, b.pt, ds, f.n_dim)) != TQP_OK) return st;
+    } else if (b.join) {
         const int32_t* dkey = static_cast<const int32_t*>(f.dim_cols[f.dim_key].data);
         if (b.dpush >= 0) {
             SrcKeepCol ds{dkey, b.dkeep, static_cast<const int32_t*>(f.dim_cols[b.dpush].data), f.n_dim};
@@ -1092,7 +1104,11 @@ tqp_status gen_launch(tqp_ctx* ctx, const tqp_fragment& f, const tqp_fragment_ou
     if (b.kv)
         return b.v32 ? kv_launch<Cfg, uint32_t>(ctx, f, o, b, b.kv32, rk, rv, s)
                      : kv_launch<Cfg, uint64_t>(ctx, f, o, b, b.kv64, rk, rv, s);
-    if (b.join) {
+    if (b.pairs) {
+        if ((st = side_join(ctx, s)) != TQP_OK) return st;
+        SrcKeepRow fs{static_cast<const int32_t*>(f.fact_cols[f.fact_key].data), b.fkeep, N};
+        if ((st = pair_probe(ctx, s, b.pt, fs, N, b.li, b.ri, J, b.d_join)) != TQP_OK) return st;
+    } else if (b.join) {
         const int32_t* fkey = static_cast<const int32_t*>(f.fact_cols[f.fact_key].data);
         const int64_t* fsort_cnt;
         if (b.fpush) {
@@ -1364,7 +1380,7 @@ extern "C" tqp_status tqp_fragment_run(tqp_ctx* ctx, const tqp_fragment* f, cons
             GenBufs<Cfg> g;
             Arena table;
             gen_reserve<Cfg>(table, ctx, fd, *o, g, sp);
-            if (!g.table) break;
+            if (!g.table && !g.pairs) break;
             if (table.total() <= sorts.total()) { spread = sp; break; }
         }
         GenBufs<Cfg> b;
