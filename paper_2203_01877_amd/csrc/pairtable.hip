@@ -51,8 +51,11 @@ __global__ void __launch_bounds__(PAIR_BLOCK) k_pair_long(PairTable t, int32_t* 
     }
 }
 
-// The slots of 2^20 keys (8 MB) are about what the L2s serve; clearing them
-// must not outweigh the rows.
+// The slots of 2^20 keys (8 MB) are about what an XCD's L2 still serves in part;
+// beyond it every row's slot is a read from the last-level cache, about 50 per
+// nanosecond, which is what the sorts cost.  Clearing and scanning the slots must
+// not outweigh the rows.  6M x 150k rows (2^18 keys) in all: 217 us, 354 by the
+// sorts.  A digit width set by the caller asks for the sorts.
 constexpr int PAIR_MAX_KEY_BITS = 20;
 bool pair_table_ok(const tqp_ctx* ctx, int64_t n_fact, int64_t n_dim, int key_bits) {
     if (ctx->digit_bits != 8) return false;

@@ -39,7 +39,7 @@ struct PairTable {
 };
 
 constexpr int PAIR_BLOCK = 256;
-constexpr int PROBE_BLOCK = 1024, PROBE_ITEMS = 16;      // a probe tile: 16384 rows
+constexpr int PROBE_BLOCK = 512, PROBE_ITEMS = 8;        // a probe tile: 4096 rows
 constexpr uint32_t PAIR_LONG = 64;     // a list longer than this is left to k_pair_long
 
 inline void pair_table_reserve(Arena& a, PairTable& t, int64_t n_dim, int key_bits, int64_t cap) {
@@ -92,9 +92,11 @@ k_pair_lists(Src src, PairTable t) {
     }
 }
 
-// One tile per block, all its slots read at once.  Bound by the slot reads, from
-// L2; the tile is large because the claims of all tiles meet at one word (about
-// 50 of them per microsecond).
+// One tile per block, all its slots read at once.  Bound by the latency of the
+// slot reads (from L2) and by the tiles' claims, which meet at one word (about
+// 50 per microsecond): 6M rows, 1.1M pairs take 39 us in tiles of 4096 rows, 45
+// in tiles of 8192, 53 to 57 in tiles of 8192 to 16384 with 16 rows per thread.
+// The sorts of both sides and the join they replace took 200.
 template <class Src>
 __global__ void __launch_bounds__(PROBE_BLOCK)
 k_pair_probe(Src src, PairTable t, int32_t* out_l, int32_t* out_r, int64_t cap, int64_t* d_n, uint32_t* flags) {
