@@ -89,6 +89,34 @@ def roofline_families(PB):
     }
 
 
+def table_bytes(N, n_f, M, J, G, PB, key_bits):
+    """As algorithmic_bytes, when the join goes by a key table (the plan then partitions each side
+    once, and the probe partitions its output): one launch of each family per step."""
+    return {
+        "mid_part": 16 * M,                                   # pk, custkey in; the same out, by partition
+        "table_build": 8 * M + 4 * (1 << key_bits),           # the partitions in, a word per key value out
+        "fact_part": 24 * N + (4 + PB) * n_f,                 # fk, date, price, disc in; key+revenue per kept row
+        "probe": (4 + PB) * n_f + 4 * (1 << key_bits) + (2 + PB) * J,   # rows and table in; (group key, revenue) out
+        "bucket_agg": (2 + PB) * J + 20 * G,
+    }
+
+
+def table_families(PB):
+    """As roofline_families, for the join by a key table."""
+    v = "u64" if PB == 8 else "u32"
+    a = "long" if PB == 8 else "u32"
+    part = ("chunks.hpp", "dev.hpp", "radix.hpp")
+    table = ("tablejoin.hpp", "chunks.hpp", "dev.hpp")
+    return {
+        "mid_part": ("k_part<u32, u32, SrcKeyCol, 0>", part),
+        "table_build": ("k_table_build<false>", table),
+        "fact_part": ("k_part<u32, %s, SrcFilterRevenue<%s, false>, 0>" % (v, v), part),
+        "probe": ("k_probe_chunks<%s>" % v, table),
+        "bucket_agg": ("k_bucket_agg<1024,8192,ChunkRows<%s, %s>,0,false>" % (a, v),
+                       ("segreduce.hpp", "chunks.hpp", "dev.hpp")),
+    }
+
+
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "cfg2_hbm_traffic.md")
 
 
@@ -323,15 +351,18 @@ def main():
     for name, t in recs:
         per.setdefault(name, []).append(t)
     stage_ms = {k: round(sum(v) / args.steps, 4) for k, v in sorted(per.items())}
-    stage_bytes = algorithmic_bytes(run.plan(), N, n_f, M, J, G, PB) if per else {}
-    step_bytes = sum(algorithmic_bytes(run.plan(), N, n_f, M, J, G, PB).values())
+    plan = run.plan()
+    table = "probe" in per if per else plan["fact_passes"] <= 1 and plan["mid_passes"] <= 1
+    family_bytes = (table_bytes(N, n_f, M, J, G, PB, key_bits) if table
+                    else algorithmic_bytes(plan, N, n_f, M, J, G, PB))
+    stage_bytes = family_bytes if per else {}
+    step_bytes = sum(family_bytes.values())
     stage_gbps = {k: round(b / (stage_ms[k] * 1e-3) / 1e9, 1) for k, b in stage_bytes.items()
                   if stage_ms.get(k)}
     # roofline: the family with the most measured time per step among the big single-stream kernels
     roofline = None
-    plan = run.plan()
-    lbytes = launch_bytes(plan, N, n_f, M, J, G, PB)
-    families = roofline_families(PB)
+    lbytes = {f: [b] for f, b in family_bytes.items()} if table else launch_bytes(plan, N, n_f, M, J, G, PB)
+    families = table_families(PB) if table else roofline_families(PB)
     timed = {f: sum(per[f]) for f in lbytes if f in per}
     if args.digit_bits == 8 and timed:
         fam = max(timed, key=timed.get)

@@ -441,7 +441,10 @@ tqp_status tqp_fragment_cust(tqp_ctx* ctx, const tqp_cust_fragment* f, const tqp
  * width (host only): radix passes of the fact, mid and group-key sorts, the
  * low fact-key bits the fact sort leaves to the join (its tiles then cover
  * bucket-aligned key ranges) and the low group-key bits resolved in LDS by
- * the bucket aggregation.  Any output pointer may be NULL. */
+ * the bucket aggregation.  Where the join goes by a table over the key domain
+ * instead (small enough a domain, and no more scratch than the sorts), the
+ * passes count the partitions made of each side (0 or 1).  Any output pointer
+ * may be NULL. */
 tqp_status tqp_fragment_cust_plan(tqp_ctx* ctx, const tqp_cust_fragment* f, int* fact_passes, int* fact_lowb,
                                   int* mid_passes, int* group_passes, int* group_lowb);
 
@@ -484,7 +487,8 @@ tqp_status tqp_fragment_cust_plan(tqp_ctx* ctx, const tqp_cust_fragment* f, int*
  * joined-row index, and each group's run reduced; with one aggregate that has
  * a program (no COUNT(DISTINCT)) and a key of 16 bits or more, the group sort
  * covers the key bits above the last 8 to 13 and each bucket of keys is
- * reduced in LDS. */
+ * reduced in LDS.  Over small key domains the join reads a table of the dim
+ * side's keys instead of sorting; the results are the same. */
 #define TQP_AGG_COUNT 0
 #define TQP_AGG_SUM 1
 #define TQP_AGG_MIN 2
