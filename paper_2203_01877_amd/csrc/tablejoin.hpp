@@ -117,9 +117,9 @@ void table_join_reserve(Arena& a, const tqp_ctx* ctx, TableJoin<V>& j, int64_t n
 // One block per slice.  SORTED: the dim rows are n rows sorted by key, those
 // of the slice one range; else the chunk list of the slice's partition, whose
 // other slices' rows are skipped.  Bound by latency and by the slices' turns
-// (one block of 128 KB LDS per CU, 2^26 keys in 2048 slices): 147 us for 15M
-// rows and 256 MB of table (every slice reads its partition, eight slices, from L2); slices of 2^14 keys read every partition
-// twice as often and are slower.
+// (one block of 128 KB LDS per CU, 2^25 keys in 1024 slices): 147 us for 15M
+// rows and 128 MB of table, each partition read by its four slices; slices of
+// 2^14 keys read every partition twice as often and are slower.
 constexpr int TJ_BUILD_BLOCK = 1024;
 template <bool SORTED>
 __global__ void __launch_bounds__(TJ_BUILD_BLOCK)
