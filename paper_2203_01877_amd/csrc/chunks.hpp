@@ -9,17 +9,13 @@
 // where a sort pass would need the partitions' counts first (a read of every
 // key) and the tiles' offsets (a look-back per tile).
 #pragma once
+#include "chunkpool.hpp"
 #include "dev.hpp"
 #include "host.hpp"
 #include "radix.hpp"
 
 namespace tqp {
 
-// Rows per chunk.  Every block leaves a chunk of each partition part-filled:
-// at 60M rows in 143 partitions by 512 blocks the lists are 75% full with 256
-// rows per chunk and 86% with 128, and the probe over them takes 483 and
-// 444 us.
-constexpr int CHUNK = 128;
 constexpr int CHUNK_GROUP = 4096 / CHUNK;      // chunks a wave takes at a time, one number per lane
 constexpr int PART_BLOCK = 512;
 constexpr int PART_WAVES = 4;          // waves per SIMD: two blocks per CU, at most 128 VGPRs
@@ -33,11 +29,6 @@ constexpr int PART_BLOCKS_PER_CU = 2;  // what the staged tile leaves room for
 template <class V> struct PartItems { static constexpr int value = sizeof(V) <= 4 ? 16 : 12; };
 template <class V> constexpr int part_tile() { return PART_BLOCK * PartItems<V>::value; }
 
-// One word of the pool counts what tiles have claimed: rows in the low 40
-// bits, chunks above them.
-constexpr int POOL_ROW_BITS = 40;
-constexpr uint64_t POOL_ROW_MASK = (uint64_t(1) << POOL_ROW_BITS) - 1;
-
 // A chunk list.  KT: uint32_t, or uint16_t when the bits below the partition
 // number fit it.
 template <class KT, class V>
@@ -50,7 +41,7 @@ struct Chunks {
     uint32_t* first = nullptr;         // [partitions] first entry of each partition in the list
     uint32_t* dcount = nullptr;        // [partitions] chunks of each partition (zero on entry)
     uint32_t* cursor = nullptr;        // [partitions] chunks listed (zero on entry)
-    uint64_t* pool = nullptr;          // rows and chunks claimed (zero on entry)
+    uint64_t* pool = nullptr;          // [POOL_WORDS] rows and chunks claimed, rows past the capacity (zero on entry)
     uint32_t* open = nullptr;          // [nblocks][partitions] each block's open chunks, or null (part_reopen)
     int64_t nchunk = 0;                // chunks in the pool
     int64_t row_cap = 0;               // rows beyond this are counted but not kept
@@ -73,9 +64,7 @@ inline int part_bits_for(int64_t rows, int nblocks, int max_bits) {
     return bits < max_bits ? bits : max_bits;
 }
 
-// row_cap rows from at most nblocks blocks: every block may leave one chunk
-// of each partition part-filled (and the tile that crosses row_cap claims
-// chunks for rows it drops).
+// row_cap rows from at most nblocks blocks.
 template <class KT, class V>
 void chunks_reserve(Arena& a, Chunks<KT, V>& c, int64_t row_cap, int nblocks, int key_bits, int part_bits) {
     const int parts = 1 << part_bits;
@@ -83,10 +72,10 @@ void chunks_reserve(Arena& a, Chunks<KT, V>& c, int64_t row_cap, int nblocks, in
     c.nblocks = nblocks;
     c.part_bits = part_bits;
     c.shift = key_bits - part_bits;
-    c.nchunk = row_cap / CHUNK + (int64_t)nblocks * parts + part_tile<V>() / CHUNK + 1;
+    c.nchunk = pool_chunks(row_cap, nblocks, parts, part_tile<V>());
     c.dcount = a.zero<uint32_t>(parts);
     c.cursor = a.zero<uint32_t>(parts);
-    c.pool = a.zero<uint64_t>(1);
+    c.pool = a.zero<uint64_t>(POOL_WORDS);
     c.keys = a.scratch<KT>(c.nchunk * CHUNK);
     c.vals = a.scratch<V>(c.nchunk * CHUNK);
     c.label = a.scratch<uint8_t>(c.nchunk);
@@ -113,6 +102,8 @@ struct PartSmem {
     uint16_t fill[PART_MAX];           // rows in the open chunk (CHUNK: none open)
     uint32_t scratch[BLOCK / WAVE];
     uint64_t claim;
+    uint64_t over;                     // rows counted after the capacity was reached
+    uint32_t full;                     // it was: the block claims nothing more
 };
 
 template <class KT, class V, int BLOCK>
@@ -121,12 +112,15 @@ __device__ __forceinline__ void part_init(PartSmem<V, BLOCK>& sm) {
         sm.fill[d] = CHUNK;
         sm.cur[d] = 0;
     }
+    if (threadIdx.x == 0) sm.over = sm.full = 0;
 }
 
 // Moves the block's tile (the items of each thread whose key is not PART_NONE)
-// into the chunk list.  Called by the whole block.
+// into the chunk list; false, to the whole block, once the list's capacity is
+// reached (a later tile's rows are then only counted).  Called by the whole
+// block.
 template <class KT, class V, int BLOCK>
-__device__ __forceinline__ void part_tile_rows(const Chunks<KT, V>& out, int parts,
+__device__ __forceinline__ bool part_tile_rows(const Chunks<KT, V>& out, int parts,
                                                const uint32_t (&key)[PartSmem<V, BLOCK>::ITEMS],
                                                const V (&val)[PartSmem<V, BLOCK>::ITEMS], PartSmem<V, BLOCK>& sm) {
     constexpr int ITEMS = PartSmem<V, BLOCK>::ITEMS;
@@ -137,6 +131,13 @@ __device__ __forceinline__ void part_tile_rows(const Chunks<KT, V>& out, int par
     asm volatile("" : "+s"(shift));
     if (tid < PART_MAX) sm.cnt[tid] = 0;
     __syncthreads();                   // also: the previous tile's rows are written out
+    if (sm.full) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) n += popc64(ballot(key[j] != PART_NONE));
+        if (lane_id() == 0 && n) atomicAdd(reinterpret_cast<unsigned long long*>(&sm.over), (unsigned long long)n);
+        return false;
+    }
     uint32_t pos[ITEMS];
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j)
@@ -148,14 +149,14 @@ __device__ __forceinline__ void part_tile_rows(const Chunks<KT, V>& out, int par
     if (tid < parts) {
         c = sm.cnt[tid];
         room = CHUNK - sm.fill[tid];
-        need = c > room ? (c - room + CHUNK - 1) / CHUNK : 0;
+        need = chunks_needed(c, sm.fill[tid]);
     }
     uint32_t tot;
     const uint32_t excl = block_excl_sum<BLOCK>((need << 16) | c, sm.scratch, &tot);
     const uint32_t total = tot & 0xFFFFu;
     uint64_t claim = 0;                // in flight while the tile is staged
     if (tid == 0)
-        claim = __hip_atomic_fetch_add(out.pool, ((uint64_t)(tot >> 16) << POOL_ROW_BITS) | total, __ATOMIC_RELAXED,
+        claim = __hip_atomic_fetch_add(out.pool, pool_add(total, tot >> 16), __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
     const uint32_t s = excl & 0xFFFFu;
     if (tid < parts) sm.start[tid] = (uint16_t)s;
@@ -171,13 +172,10 @@ __device__ __forceinline__ void part_tile_rows(const Chunks<KT, V>& out, int par
     }
     if (tid == 0) sm.claim = claim;
     __syncthreads();
-    claim = sm.claim;
-    const int64_t row0 = (int64_t)(claim & POOL_ROW_MASK);
-    const int64_t chunk0 = (int64_t)(claim >> POOL_ROW_BITS);
-    int64_t keep = out.row_cap - row0;
-    if (keep > total) keep = total;
-    if (keep < 0 || chunk0 + (tot >> 16) > out.nchunk) keep = 0;
-    const uint32_t base = (uint32_t)(chunk0 + (excl >> 16));
+    const PoolClaim pc = pool_claim(sm.claim, total, tot >> 16, out.row_cap, out.nchunk);
+    const int64_t keep = pc.keep;
+    const uint32_t base = (uint32_t)(pc.chunk0 + (excl >> 16));
+    if (tid == 0) sm.full = pc.full;
     uint32_t added = 0;                // chunks the partition takes
     uint32_t full = ~0u;               // its open chunk, now full
     if (tid < parts) {
@@ -202,7 +200,7 @@ __device__ __forceinline__ void part_tile_rows(const Chunks<KT, V>& out, int par
     if (full != ~0u) out.rows[full] = CHUNK;
     // every chunk claimed gets a label, so that the list holds each one; the
     // rows a tile drops at row_cap may leave some of them empty
-    const uint32_t claimed = base < out.nchunk ? (need < out.nchunk - base ? need : (uint32_t)(out.nchunk - base)) : 0;
+    const uint32_t claimed = chunks_in_pool(base, need, out.nchunk);
     if (tid < parts && claimed) {
         atomic_add(&out.dcount[tid], claimed);
         for (uint32_t i = 0; i < claimed; ++i) {
@@ -222,12 +220,16 @@ __device__ __forceinline__ void part_tile_rows(const Chunks<KT, V>& out, int par
             out.vals[g] = sm.vals[p];
         }
     }
+    return !pc.full;
 }
 
-// Row counts of the chunks the block leaves part-filled, and where they are.
+// Row counts of the chunks the block leaves part-filled, and where they are;
+// the rows it counted past the capacity.  Called by the whole block.
 template <class KT, class V, int BLOCK>
 __device__ __forceinline__ void part_finish(const Chunks<KT, V>& out, int parts, PartSmem<V, BLOCK>& sm) {
     const int d = threadIdx.x;
+    __syncthreads();
+    if (d == 0 && sm.over) atomic_add(out.pool + 1, sm.over);
     if (d >= parts) return;
     if (sm.fill[d] < CHUNK) out.rows[sm.cur[d]] = sm.fill[d];
     if (out.open) out.open[(int64_t)blockIdx.x * parts + d] = sm.fill[d] < CHUNK ? sm.cur[d] : ~0u;
@@ -243,6 +245,7 @@ __device__ __forceinline__ void part_reopen(const Chunks<KT, V>& out, int parts,
         sm.cur[d] = c != ~0u ? c : 0;
         sm.fill[d] = c != ~0u ? (uint16_t)out.rows[c] : CHUNK;
     }
+    if (threadIdx.x == 0) sm.over = sm.full = 0;
 }
 
 // ------------------------------------------------------------------ the lists

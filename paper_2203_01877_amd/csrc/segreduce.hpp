@@ -283,7 +283,7 @@ struct SortedRows {
 // Rows in the chunk list of a group partition (V: the value's bits).  A wave
 // takes a group of chunks at a time, eight of them in flight; when they hold few rows
 // (a small input spread over many blocks), their rows laid end to end, so that
-// the lanes are full and all loads in flight.  finish: the rows claimed (a
+// the lanes are full and all loads in flight.  finish: the rows counted (a
 // join's size) go to *d_rows, more than the list keeps raise the capacity
 // flag.
 template <class VT, class V>
@@ -346,7 +346,7 @@ struct ChunkRows {
     }
     __device__ __forceinline__ void finish(int64_t b, uint32_t* flags) const {
         if (b != 0 || threadIdx.x != 0) return;
-        const int64_t n = (int64_t)(*c.pool & POOL_ROW_MASK);
+        const int64_t n = pool_rows(c.pool[0], c.pool[1]);
         if (d_rows) *d_rows = n;
         if (n > c.row_cap) set_flag(flags, FLAG_CAPACITY);
     }

@@ -14,7 +14,8 @@ k_chunks_list(const uint8_t* label, const uint64_t* pool, const uint32_t* dcount
     uint32_t tot;
     const uint32_t f = block_excl_sum<LIST_BLOCK>(tid < parts ? dcount[tid] : 0, s_scan, &tot);
     if (blockIdx.x == 0 && tid < parts) first[tid] = f;
-    // chunks are claimed in order; those past the pool's end were not filled
+    // chunks are claimed in order, each by one tile; those past the pool's end
+    // were neither labelled nor counted
     int64_t n = (int64_t)(*pool >> POOL_ROW_BITS);
     if (n > nchunk) n = nchunk;
     const int64_t i0 = ((int64_t)blockIdx.x * LIST_BLOCK + tid) * LIST_ITEMS;

@@ -450,7 +450,7 @@ k_probe_lists(Place place, JoinTable t, Spill sp, Chunks<uint16_t, V> out, int p
     const int64_t n = (int64_t)*sp.n;
     if ((int64_t)blockIdx.x * ROWS >= n) return;
     part_reopen<uint16_t, V, LISTS_BLOCK>(out, parts, sm);
-    bool wide = false;
+    bool wide = false, room = true;
     for (int64_t r0 = (int64_t)blockIdx.x * ROWS; r0 < n; r0 += (int64_t)gridDim.x * ROWS) {
         __syncthreads();                              // the previous rows are expanded
         int64_t len[PER], mine = 0;
@@ -475,7 +475,8 @@ k_probe_lists(Place place, JoinTable t, Spill sp, Chunks<uint16_t, V> out, int p
             at += len[q];
         }
         __syncthreads();
-        for (int64_t q0 = 0; q0 < total; q0 += TILE) {
+        int64_t q0 = 0;
+        for (; room && q0 < total; q0 += TILE) {
             uint32_t key[ITEMS];
             V val[ITEMS];
 #pragma unroll
@@ -492,8 +493,11 @@ k_probe_lists(Place place, JoinTable t, Spill sp, Chunks<uint16_t, V> out, int p
                 key[j] = (e & ~TJ_WIDE) - 1;          // past the end: PART_NONE
                 val[j] = s_val[lo];
             }
-            part_tile_rows<uint16_t, V, LISTS_BLOCK>(out, parts, key, val, sm);
+            room = part_tile_rows<uint16_t, V, LISTS_BLOCK>(out, parts, key, val, sm);
         }
+        // pairs past the capacity are counted, not walked through: a key that
+        // is frequent on both sides has more of them than a launch could
+        if (tid == 0 && q0 < total) sm.over += (uint64_t)(total - q0);
     }
     part_finish<uint16_t, V, LISTS_BLOCK>(out, parts, sm);
     if (__any(wide) && l == 0) set_flag(flags, FLAG_KEY_RANGE);
