@@ -73,6 +73,11 @@ constexpr int HA_LDS_BYTES = 65536;         // LDS of a partition's table
 constexpr int64_t HA_MANY_ROWS = int64_t(1) << 21;
 constexpr int ha_local_bytes(bool dist, int64_t n) { return dist || n >= HA_MANY_ROWS ? 131072 : 65536; }
 constexpr uint32_t HA_PROBE_LIMIT = 4096;
+// Probes of the per-block table, at most half full while there are no more
+// groups than gcap.  With more of them it fills up, and a row that walked all
+// of its slots would cost a launch a hundred times its time (6M rows of 1M
+// groups, gcap 4096: 118 ms; 2.3 so).
+constexpr int HA_LOCAL_PROBE = 32;
 constexpr unsigned long long ORD_BIAS = 1ull << 63;
 
 struct alignas(32) HaSlot {
@@ -111,6 +116,12 @@ struct HaArgs {
     uint32_t gcap;
     uint32_t* flags;
 };
+
+// The capacity flag, set by many rows of an input with more groups than gcap:
+// one word for all of them, so it is read before it is written.
+__device__ __forceinline__ void ha_over_capacity(const HaArgs& a) {
+    if (!(ld_relaxed(a.flags) & FLAG_CAPACITY)) set_flag(a.flags, FLAG_CAPACITY);
+}
 
 __device__ __forceinline__ int64_t ha_rows(const HaArgs& a) {
     int64_t n = a.n_upper;
@@ -154,7 +165,7 @@ __device__ __forceinline__ void ha_find(const HaArgs& a, const uint32_t (&k1)[IT
                 if (ld_relaxed(a.d_groups) >= a.gcap) {
                     old = ld_relaxed(&a.table[s[j]].key1);
                     if (old == 0u) {
-                        set_flag(a.flags, FLAG_CAPACITY);     // a new group beyond gcap
+                        ha_over_capacity(a);                  // a new group beyond gcap
                         live[j] = false;
                         continue;
                     }
@@ -174,7 +185,7 @@ __device__ __forceinline__ void ha_find(const HaArgs& a, const uint32_t (&k1)[IT
     }
 #pragma unroll
     for (int j = 0; j < IT; ++j)
-        if (live[j]) set_flag(a.flags, FLAG_CAPACITY);      // probe limit reached
+        if (live[j]) ha_over_capacity(a);                   // probe limit reached
 }
 
 // Inserts the pairs (key + 1, d) into the set; ins[j] is true for the item
@@ -294,8 +305,8 @@ __global__ void __launch_bounds__(HA_BLOCK) k_ha_global(HaArgs a) {
 // the first slots of all items read at once: bound by the latency of LDS and,
 // with many groups, by the merges' global atomics (30M rows, 1000 groups, every
 // statistic: 411 us with 256 threads per table, 130 so).  A row whose LDS
-// probe fails (more groups than the LDS table holds, which only an input with
-// more than gcap groups reaches) goes to the global table directly.
+// probe fails (a run of HA_LOCAL_PROBE slots of other groups) goes to the
+// global table directly.
 template <bool VAL, bool MINMAX, bool DIST>
 constexpr int ha_lds_slot_bytes() {
     return 8 + (VAL ? 8 : 0) + (MINMAX ? 16 : 0) + (DIST ? 4 : 0);
@@ -365,7 +376,7 @@ __global__ void __launch_bounds__(HA_LOCAL_BLOCK) k_ha_local(HaArgs a, int lg, i
             spill[j] = false;
             if (!in[j]) continue;
             uint32_t s = home[j];
-            for (int p = 0; p < S; ++p) {
+            for (int p = 0; p < HA_LOCAL_PROBE; ++p) {
                 uint32_t cur = p ? s_key[s] : key0[j];
                 if (cur == 0u) cur = atomicCAS(&s_key[s], 0u, k1[j]);
                 if (cur == 0u || cur == k1[j]) { ls[j] = (int32_t)s; break; }
