@@ -29,3 +29,48 @@ def test_many_groups_over_capacity(hip, minmax, cap):
     kk, s, c = (got[x][:m].cpu().numpy() for x in ("key", "sum", "cnt"))
     assert len(np.unique(kk)) == m and np.array_equal(s, c) and np.all(c <= np.bincount(key, minlength=g)[kk])
     assert ms < 10.0
+
+
+def _groups(shape, n, r):
+    lane = np.arange(n) % 64
+    if shape == "one":
+        return np.full(n, 5)
+    if shape == "skew":                              # 90% of the rows on one group
+        return np.where(r.random(n) < 0.9, 77, r.integers(0, 900, n))
+    if shape == "half":                              # 32 lanes of a wave on the group of its first row
+        return np.where(lane % 2 == 0, 3, 4 + lane)
+    if shape == "less":                              # 31 lanes: one by one
+        return np.where((lane % 2 == 0) & (lane != 62), 3, 4 + lane)
+    return np.where(r.random(n) < 0.5, -1, 6)        # negative keys left out, some in a wave's first row
+
+
+@pytest.mark.parametrize("n", [1, 63, 4_097, 100_003])
+@pytest.mark.parametrize("shape", ["one", "skew", "half", "less", "negative"])
+@pytest.mark.parametrize("cols", ["count", "sum", "minmax", "distinct"])
+def test_rows_of_one_group(hip, n, shape, cols):
+    """Waves whose lanes share a group, every set of columns, values up to the ends of int64."""
+    ctx = hip.Context(0)
+    r = np.random.default_rng(n)
+    key = _groups(shape, n, r).astype(np.int32)
+    val = r.integers(-(1 << 62), 1 << 62, n)
+    val[:: 7], val[3:: 11] = np.iinfo(np.int64).min, np.iinfo(np.int64).max
+    d = r.integers(0, 9, n).astype(np.int32)
+    k, v, dv = _dev(key, val, d)
+    got = hip.hash_groupby(ctx, k, v if cols != "count" else None, dval=dv if cols == "distinct" else None, gcap=1000,
+                           minmax=cols in ("minmax", "distinct"))
+    keep = key >= 0
+    assert ctx.errors() == (0 if keep.all() else hip.DEVERR_KEY_RANGE)
+    key, val, d = key[keep], val[keep], d[keep]
+    u, inv = np.unique(key, return_inverse=True)
+    m = int(got["d_ngroups"])
+    o = np.argsort(got["key"][:m].cpu().numpy())
+    col = lambda c: got[c][:m].cpu().numpy()[o]
+    assert np.array_equal(col("key"), u) and np.array_equal(col("cnt"), np.bincount(inv, minlength=len(u)))
+    if cols != "count":
+        with np.errstate(over="ignore"):
+            assert np.array_equal(col("sum"), np.array([val[inv == i].sum() for i in range(len(u))], dtype=np.int64))
+    if cols in ("minmax", "distinct"):
+        assert np.array_equal(col("min"), np.array([val[inv == i].min() for i in range(len(u))], dtype=np.int64))
+        assert np.array_equal(col("max"), np.array([val[inv == i].max() for i in range(len(u))], dtype=np.int64))
+    if cols == "distinct":
+        assert np.array_equal(col("ndist"), np.array([len(np.unique(d[inv == i])) for i in range(len(u))]))
