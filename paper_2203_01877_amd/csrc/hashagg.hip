@@ -969,9 +969,12 @@ int ha_lds_log2(int64_t gcap, int64_t n) {
 // Blocks of the local kernel, at most one per CU: the rows' work falls with
 // their number, that of the merges (blocks * groups) rises with it.  30M rows
 // take 55 us of row work in 256 blocks, merging 1000 groups of every block 85:
-// both are the same in 1.2 * sqrt(n / gcap) blocks.
-inline int ha_local_blocks(const tqp_ctx* ctx, int64_t n, int64_t gcap) {
-    const int64_t even = (int64_t)(1.2 * std::sqrt((double)n / (double)(gcap < 1 ? 1 : gcap))) + 1;
+// both are the same in 1.2 * sqrt(n / gcap) blocks.  With distinct counts a row
+// is also tried in the global set, which weighs more than ten times its LDS
+// work: 1M rows over 2000 groups take 365 us in 27 blocks, 183 in 90; over 1000
+// groups 289 in 38 and 143 in 127; 6M over 300 groups 207 in 170, 221 in 256.
+inline int ha_local_blocks(const tqp_ctx* ctx, int64_t n, int64_t gcap, bool dist) {
+    const int64_t even = (int64_t)((dist ? 4.0 : 1.2) * std::sqrt((double)n / (double)(gcap < 1 ? 1 : gcap))) + 1;
     return grid_for(n, (int64_t)HA_LOCAL_BLOCK * HA_ITEMS, std::min<int64_t>(even, ctx->num_cus));
 }
 
@@ -994,7 +997,7 @@ tqp_status ha_run(tqp_ctx* ctx, const HaArgs& a, int64_t gcap, int64_t n, hipStr
         if (lds > 65536 && allowed != hipSuccess)
             return fail(TQP_ERR_HIP, "tqp_hash_groupby: %zu bytes of LDS refused", lds);
         TQP_LAUNCH(ctx, stream, "hashagg_local",
-                   k_ha_local<VAL, MINMAX, DIST><<<ha_local_blocks(ctx, n, gcap), HA_LOCAL_BLOCK, lds, stream>>>(
+                   k_ha_local<VAL, MINMAX, DIST><<<ha_local_blocks(ctx, n, gcap, DIST), HA_LOCAL_BLOCK, lds, stream>>>(
                        a, lg, pset));
     } else {
         const int grid = grid_for(n, (int64_t)HA_BLOCK * HA_ITEMS, (int64_t)ctx->num_cus * per_cu_global);

@@ -74,3 +74,22 @@ def test_rows_of_one_group(hip, n, shape, cols):
         assert np.array_equal(col("max"), np.array([val[inv == i].max() for i in range(len(u))], dtype=np.int64))
     if cols == "distinct":
         assert np.array_equal(col("ndist"), np.array([len(np.unique(d[inv == i])) for i in range(len(u))]))
+
+
+@pytest.mark.parametrize("n,g", [(200_000, 1_000), (1_000_000, 2_000), (1_000_000, 65), (300_001, 64)])
+@pytest.mark.parametrize("cols", ["distinct", "sum", "minmax"])
+def test_distinct_grid(hip, n, g, cols):
+    """COUNT(DISTINCT) with few rows per group: the grid of the rows' own work, every row in one block."""
+    ctx = hip.Context(0)
+    r = np.random.default_rng(g)
+    key, val, d = r.integers(0, g, n), r.integers(-1000, 1000, n), r.integers(0, 5000, n)
+    k, v, dv = _dev(key.astype(np.int32), val, d.astype(np.int32))
+    got = hip.hash_groupby(ctx, k, None if cols == "distinct" else v, dval=dv, gcap=g, minmax=cols == "minmax")
+    m = int(got["d_ngroups"])
+    assert m == len(np.unique(key)) and ctx.errors() == 0
+    o = np.argsort(got["key"][:m].cpu().numpy())
+    col = lambda c: got[c][:m].cpu().numpy()[o]
+    assert np.array_equal(col("cnt"), np.bincount(key, minlength=g))
+    assert np.array_equal(col("ndist"), np.bincount(np.unique(key * 5000 + d) // 5000, minlength=g))
+    if cols != "distinct":
+        assert np.array_equal(col("sum"), np.bincount(key, weights=val, minlength=g).astype(np.int64))
