@@ -66,12 +66,14 @@ constexpr int HA_ITEMS = 4;                 // rows per thread per step, probed 
 constexpr int HA_LDS_MIN = 256;             // slots of the per-block table: 2 * gcap (or 4 * gcap), at least this
 constexpr int HA_LDS_BYTES = 65536;         // LDS of a partition's table
 // LDS of the per-block table (of the 160 KB of a CU): 128 KB with distinct
-// counts, which have no partitioned path to fall back on, and for many rows;
-// 64 KB else.  MIN and MAX too over 2000 groups, where the table takes 128 KB:
-// 177 us for 30M rows and 92 for 6M where the partitioned path takes 488 and
-// 113, but 58 against 50 for 1M.
-constexpr int64_t HA_MANY_ROWS = int64_t(1) << 21;
-constexpr int ha_local_bytes(bool dist, int64_t n) { return dist || n >= HA_MANY_ROWS ? 131072 : 65536; }
+// counts, which have no partitioned path to fall back on, and for many rows per
+// group; 64 KB else.  Every statistic over 2048 groups: 110 us for 6M rows and
+// 100 for 4.2M where the partitioned path takes 139 and 116, 85 against 83 for
+// 2.1M; sums over 4096 groups: 121 against 139 for 9M rows, 112 against 110
+// for 6M and 88 against 74 for 2.1M.
+constexpr int64_t HA_MANY_ROWS = 2048;      // per group of gcap
+constexpr int HA_LDS_MOST = 131072;
+constexpr int ha_local_bytes(bool dist, bool many) { return dist || many ? HA_LDS_MOST : 65536; }
 constexpr uint32_t HA_PROBE_LIMIT = 4096;
 // Probes of the per-block table, at most half full while there are no more
 // groups than gcap.  With more of them it fills up, and a row that walked all
@@ -962,8 +964,8 @@ int ha_lds_log2(int64_t gcap, int64_t n) {
     // minimum-size table keeps its size: doubling it only adds clearing and
     // merging.
     const int64_t bytes = ha_lds_slot_bytes<VAL, MINMAX, DIST>();
-    if ((int64_t(1) << lg) > HA_LDS_MIN && (int64_t(1) << (lg + 1)) * bytes + set <= ha_local_bytes(DIST, 0)) return lg + 1;
-    return ((int64_t(1) << lg) * bytes + set <= ha_local_bytes(DIST, n)) ? lg : -1;
+    if ((int64_t(1) << lg) > HA_LDS_MIN && (int64_t(1) << (lg + 1)) * bytes + set <= ha_local_bytes(DIST, false)) return lg + 1;
+    return ((int64_t(1) << lg) * bytes + set <= ha_local_bytes(DIST, n >= HA_MANY_ROWS * gcap)) ? lg : -1;
 }
 
 // Blocks of the local kernel, at most one per CU: the rows' work falls with
@@ -993,7 +995,7 @@ tqp_status ha_run(tqp_ctx* ctx, const HaArgs& a, int64_t gcap, int64_t n, hipStr
         const size_t lds = ((size_t)1 << lg) * ha_lds_slot_bytes<VAL, MINMAX, DIST>() + (pset ? HA_LSET * 8 : 0);
         static const hipError_t allowed =
             hipFuncSetAttribute(reinterpret_cast<const void*>(k_ha_local<VAL, MINMAX, DIST>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, ha_local_bytes(DIST, HA_MANY_ROWS));
+                                hipFuncAttributeMaxDynamicSharedMemorySize, HA_LDS_MOST);
         if (lds > 65536 && allowed != hipSuccess)
             return fail(TQP_ERR_HIP, "tqp_hash_groupby: %zu bytes of LDS refused", lds);
         TQP_LAUNCH(ctx, stream, "hashagg_local",

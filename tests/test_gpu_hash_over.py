@@ -93,3 +93,22 @@ def test_distinct_grid(hip, n, g, cols):
     assert np.array_equal(col("ndist"), np.bincount(np.unique(key * 5000 + d) // 5000, minlength=g))
     if cols != "distinct":
         assert np.array_equal(col("sum"), np.bincount(key, weights=val, minlength=g).astype(np.int64))
+
+
+@pytest.mark.parametrize("minmax,g", [(False, 2_049), (True, 1_025)])
+@pytest.mark.parametrize("less", [0, 1])
+def test_large_table_rule(hip, minmax, g, less):
+    """The first row count per group at which a table of 128 KB takes the rows, and one row fewer."""
+    ctx = hip.Context(0)
+    n = 2048 * g - less
+    r = np.random.default_rng(g)
+    key, val = r.integers(0, g, n), r.integers(-1000, 1000, n)
+    k, v = _dev(key.astype(np.int32), val)
+    ctx.set_profiling(True)
+    got = hip.hash_groupby(ctx, k, v, gcap=g, minmax=minmax)
+    assert ("hashagg_local" in [x for x, _ in ctx.profile_read()]) == (less == 0)
+    m = int(got["d_ngroups"])
+    o = np.argsort(got["key"][:m].cpu().numpy())
+    assert m == g and ctx.errors() == 0
+    assert np.array_equal(got["cnt"][:m].cpu().numpy()[o], np.bincount(key, minlength=g))
+    assert np.array_equal(got["sum"][:m].cpu().numpy()[o], np.bincount(key, weights=val, minlength=g).astype(np.int64))
