@@ -146,6 +146,33 @@ __device__ __forceinline__ T wave_sum(T v) {
     return wave_read(wave_incl_sum(v), WAVE - 1);
 }
 
+// Lanes of a wave that hold the same key, found through 64 words of LDS per
+// wave (lane numbers by the key's hash; the last lane to write a word leads its
+// lanes).  For the live lanes: the leader of the lane's key (itself where two
+// keys meet at one word), the lane's rank among those it leads, and for the
+// leader their number.  A device-wide atomic per key and wave then takes the
+// place of one per row, which take turns on the word of a frequent key.  Called
+// by the whole wave; lds is its own WaveMatch.
+struct WaveMatch {
+    uint32_t lane[WAVE], count[WAVE];
+};
+__device__ __forceinline__ void wave_match(WaveMatch& lds, uint32_t key, bool live, int& leader, uint32_t& rank,
+                                           uint32_t& count) {
+    const int l = lane_id();
+    // volatile: the lanes of a wave run in step, the word read is the winner's
+    volatile uint32_t* const word = &lds.lane[(key * 0x9E3779B1u) >> 26];
+    volatile uint32_t* const cnt = lds.count;
+    cnt[l] = 0;
+    if (live) *word = (uint32_t)l;
+    __builtin_amdgcn_wave_barrier();
+    leader = live ? (int)*word : l;
+    if (wave_shfl(key, leader) != key) leader = l;
+    __builtin_amdgcn_wave_barrier();
+    rank = live ? atomicAdd(&lds.count[leader], 1u) : 0;
+    __builtin_amdgcn_wave_barrier();
+    count = cnt[l];
+}
+
 // Maximum / minimum over the lanes of unsigned 4- or 8-byte words.
 template <class U>
 __device__ __forceinline__ U wave_max(U v) {

@@ -109,21 +109,41 @@ __device__ __forceinline__ void acc_flush(AccSmem& sm, int64_t joined, int64_t* 
     }
 }
 
-// Dim rows [r0, r1) that pass their predicate, entered into the table.
+// Dim rows [r0, r1) that pass their predicate, entered into the table: rows of
+// one key once per wave, and the word that says that keys repeat once per
+// wave.  With an atomic per row the rows of a frequent key, and with a store
+// per further row all of them, take turns on one word (4.6 ns each): 3M dim
+// rows, half of them with one key, 20.3 ms and 0.27 so; every key twice 1.76 and
+// 0.25; every key once 0.12 both ways.
 __device__ __forceinline__ void enter_dim(const FlagsDirect& f, int64_t r0, int64_t r1, uint32_t* flags) {
-    uint32_t bad = 0;
-    for (int64_t i = r0 + threadIdx.x; i < r1; i += BLOCK) {
-        const uint32_t k = (uint32_t)f.pk[i];
-        if (f.seg[i] != f.c) continue;
-        if (k & ~f.key_mask) { bad = 1; continue; }
-        const uint32_t bit = 1u << (k & 31);
-        const uint32_t old = __hip_atomic_fetch_or(&f.bits[k >> 5], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (old & bit) {
-            atomic_add(&f.extra[k], 1u);
-            st_relaxed(f.repeats, 1u);
+    __shared__ WaveMatch s_match[BLOCK / WAVE];
+    WaveMatch& match = s_match[threadIdx.x / WAVE];
+    bool bad = false, again = false;
+    for (int64_t i0 = r0; i0 < r1; i0 += BLOCK) {
+        const int64_t i = i0 + threadIdx.x, ic = i < r1 ? i : r1 - 1;
+        const uint32_t k = (uint32_t)f.pk[ic];
+        const bool kept = i < r1 && f.seg[ic] == f.c, in = (k & ~f.key_mask) == 0;
+        bad |= kept && !in;
+        const bool live = kept && in;
+        int leader;
+        uint32_t rank, count;
+        wave_match(match, k, live, leader, rank, count);
+        if (live && leader == lane_id()) {
+            const uint32_t bit = 1u << (k & 31);
+            uint32_t* word = &f.bits[k >> 5];
+            // (a frequent key's bit is mostly set by now)
+            const uint32_t old = count > 1 && (ld_relaxed(word) & bit)
+                                     ? bit
+                                     : __hip_atomic_fetch_or(word, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t more = old & bit ? count : count - 1;
+            if (more) {
+                atomic_add(&f.extra[k], more);
+                again = true;
+            }
         }
     }
-    if (__any(bad != 0) && lane_id() == 0) set_flag(flags, FLAG_KEY_RANGE);
+    if (__any(again) && lane_id() == 0 && ld_relaxed(f.repeats) == 0) st_relaxed(f.repeats, 1u);
+    if (__any(bad) && lane_id() == 0) set_flag(flags, FLAG_KEY_RANGE);
 }
 
 __device__ __forceinline__ void table_rows(const FlagsDirect& f, int64_t r0, int64_t r1, int64_t slot, AccSmem& sm,
