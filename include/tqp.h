@@ -555,9 +555,14 @@ tqp_status tqp_fragment_run(tqp_ctx* ctx, const tqp_fragment* f, const tqp_fragm
  * descriptors to the device (synchronous).  Each fragment's results go to
  * its tqp_flags_out, exactly as tqp_fragment_flags would write them.
  * Configurations: 0 = 4-bit digits / 2048-row tiles, 1 = 8-bit / 2048,
- * 2 = 8-bit / 4096 (default), 3 = 11-bit / 4096.
+ * 2 = 8-bit / 4096 (default), 3 = 11-bit / 4096.  They are those of the sorts:
+ * a batch whose fragments all have small key domains reads tables of the dim
+ * keys instead (with the context's default digit width, and where the tables
+ * need no more scratch than the sorts' row buffers and 16 MB) and runs the
+ * same launches under each of them.
  * tqp_batch_autotune runs every configuration `reps` times on `stream`, keeps
- * the fastest and writes the mean time of each to times_ms[4] (nullable).
+ * the fastest and writes the mean time of each to times_ms[4] (nullable); for
+ * a batch by tables it times the one sequence and keeps the configuration.
  * tqp_batch_capture records the launch sequence of the chosen configuration
  * into a hipGraph (stream must not be the null stream); tqp_batch_replay
  * launches that graph.  Calls that share a batch must not overlap in time. */

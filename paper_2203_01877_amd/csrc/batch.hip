@@ -644,7 +644,12 @@ tqp_status batch_prepare(tqp_ctx* ctx, const tqp_flags_fragment* frags, const tq
     b->chosen = chosen;
     b->frags.assign(frags, frags + nf);
     b->outs.assign(outs, outs + nf);
-    b->direct = nf > 0 && std::all_of(frags, frags + nf, flags_direct_ok);
+    b->direct = nf > 0 && std::all_of(frags, frags + nf,
+                                      [&](const tqp_flags_fragment& f) { return flags_direct_ok(ctx, f); });
+    if (b->direct) {
+        const size_t table = plan_direct(b, nullptr);
+        b->direct = table <= scratch_bytes(b) + FLAGS_BATCH_SPARE && (!ws || *ws_bytes >= table);
+    }
     const size_t need = plan_all(b, nullptr, nullptr);
     if (!ws) {
         *ws_bytes = need;
@@ -740,6 +745,14 @@ tqp_status tqp_batch_autotune(tqp_batch* b, hipStream_t stream, int reps, float*
         ms /= reps;
         b->tuned_ms[c] = ms;
         if (times_ms) times_ms[c] = ms;
+        if (b->direct) {                   // one sequence for every configuration: none is faster
+            for (int d = 0; d < NCAND; ++d) {
+                if (!(b->cand_mask & (1 << d))) continue;
+                b->tuned_ms[d] = ms;
+                if (times_ms) times_ms[d] = ms;
+            }
+            break;
+        }
         if (best_ms == 0.f || ms < best_ms) { best_ms = ms; best = c; }
     }
     (void)hipEventDestroy(e0);

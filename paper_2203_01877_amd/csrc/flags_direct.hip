@@ -16,7 +16,11 @@ constexpr int BLOCKS_PER_CU = 4;
 // sort it replaces (60k x 15M rows over 2^24 keys: 138 us against 277 with the
 // sorts; 1k x 150k: 16 against 133; 60M x 1.5M: 550 against 1623).  The rule
 // leaves the fact rows out: requests over row ranges of one table then all
-// take the same form, whatever their size.
+// take the same form, whatever their size.  A digit width set by the caller
+// asks for the sorts.  The free keys are the one case in which the table needs
+// more scratch than the sorts, at most 1.1 MB of it: a caller's workspace that
+// the sorts fit and the table does not is given to the sorts, and a batch's
+// tables are bounded as a whole (FLAGS_BATCH_SPARE).
 constexpr int MAX_KEY_BITS = 26;
 constexpr int64_t FREE_KEYS = int64_t(1) << 18;
 
@@ -284,7 +288,8 @@ __global__ void __launch_bounds__(FINAL_BLOCK) k_batch_flags_final(const FlagsDi
 
 }  // namespace
 
-bool flags_direct_ok(const tqp_flags_fragment& f) {
+bool flags_direct_ok(const tqp_ctx* ctx, const tqp_flags_fragment& f) {
+    if (ctx->digit_bits != 8) return false;
     const int kb = norm_key_bits(f.key_bits);
     return kb <= MAX_KEY_BITS && (int64_t(1) << kb) <= 4 * f.n_dim + FREE_KEYS;
 }

@@ -48,7 +48,11 @@ constexpr int64_t FLAGS_BATCH_ROWS = 16384;           // fact rows of a batch it
 constexpr int64_t FLAGS_BATCH_DIM_ROWS = 1024;        // dim rows of a batch item
 
 // Whether a fragment takes the table (see flags_direct.hip for the rule).
-bool flags_direct_ok(const tqp_flags_fragment& f);
+bool flags_direct_ok(const tqp_ctx* ctx, const tqp_flags_fragment& f);
+// A batch's tables may take this much more than the row buffers of its sorts:
+// what a single fragment's free keys cost at most, sixteen times, or 4 us of
+// clearing where the sorts take more launches than that.
+constexpr size_t FLAGS_BATCH_SPARE = size_t(16) << 20;
 // Whether the fact blocks of a single fragment count its dim rows in LDS.
 bool flags_direct_lds(const tqp_flags_fragment& f);
 int64_t flags_direct_words(const tqp_flags_fragment& f);      // words of `bits`

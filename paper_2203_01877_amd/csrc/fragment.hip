@@ -426,7 +426,12 @@ tqp_status tqp_fragment_flags(tqp_ctx* ctx, const tqp_flags_fragment* f, const t
     if (!ctx) return fail(TQP_ERR_INVALID, "null context");
     tqp_status st = check_flags(f, o);
     if (st != TQP_OK) return st;
-    if (flags_direct_ok(*f)) return flags_direct_run(ctx, *f, *o, ws, ws_bytes, stream);
+    if (flags_direct_ok(ctx, *f)) {
+        // (a workspace that the table does not fit may still do for the sorts)
+        st = flags_direct_run(ctx, *f, *o, ws, ws_bytes, stream);
+        if (st != TQP_ERR_WORKSPACE) return st;
+        clear_error();
+    }
     return with_radix_cfg(ctx->digit_bits, [&](auto cfg) -> tqp_status {
         using Cfg = decltype(cfg);
         FlagsBufs<Cfg> b;
