@@ -121,6 +121,7 @@ void table_join_reserve(Arena& a, const tqp_ctx* ctx, TableJoin<V>& j, int64_t n
 // rows and 128 MB of table, each partition read by its four slices; slices of
 // 2^14 keys read every partition twice as often and are slower.
 constexpr int TJ_BUILD_BLOCK = 1024;
+constexpr int TJ_SAME = 8;             // lanes of a wave with one key from which they are taken together
 template <bool SORTED>
 __global__ void __launch_bounds__(TJ_BUILD_BLOCK)
 k_table_build(JoinTable t, const uint32_t* dkey, const uint32_t* dval, int64_t n) {
@@ -143,16 +144,19 @@ k_table_build(JoinTable t, const uint32_t* dkey, const uint32_t* dval, int64_t n
         if (tid == 0) s_many = 0;
         __syncthreads();
     };
-    // f(slot, entry) for every dim row of the slice
+    // f(slot, entry, frequent slot) for every dim row of the slice
     auto each = [&](auto f) {
         constexpr int U = 8;                          // loads in flight per thread
         auto enter = [&](const uint32_t (&k)[U], const uint32_t* const (&vp)[U], const bool (&in)[U]) {
             uint32_t v[U];
 #pragma unroll
             for (int q = 0; q < U; ++q) v[q] = *vp[q];
+            // frequent: the key of the wave's first row, met by several lanes, or ~0
+            uint32_t frequent = __builtin_amdgcn_readfirstlane(k[0]);
+            if (popc64(ballot(in[0] && k[0] == frequent)) < TJ_SAME) frequent = ~0u;
 #pragma unroll
             for (int q = 0; q < U; ++q)
-                if (in[q]) f(k[q], ((v[q] & t.group_mask) + 1) | (v[q] & ~t.group_mask ? TJ_WIDE : 0u));
+                if (in[q]) f(k[q], ((v[q] & t.group_mask) + 1) | (v[q] & ~t.group_mask ? TJ_WIDE : 0u), frequent);
         };
         uint32_t k[U];
         const uint32_t* vp[U];
@@ -199,16 +203,27 @@ k_table_build(JoinTable t, const uint32_t* dkey, const uint32_t* dval, int64_t n
         }
     };
     clear();
-    each([&](uint32_t k, uint32_t e) {
+    each([&](uint32_t k, uint32_t e, uint32_t) {
         if (atomicCAS(&s_slot[k], 0u, e) != 0) s_many = 1;
     });
     __syncthreads();
     if (s_many) {
         // some key has several rows: count the rows of every key, give each
-        // such key a list, and enter the rows again
+        // such key a list, and enter the rows again.  Lanes with a frequent key
+        // are taken together: its slice is one block's work, and its rows would
+        // take turns on one LDS word (750k rows with one key: 1944 us one by
+        // one, 1161 so).
         __syncthreads();
         clear();
-        each([&](uint32_t k, uint32_t) { atomicAdd(&s_slot[k], 1u); });
+        each([&](uint32_t k, uint32_t, uint32_t frequent) {
+            if (frequent == ~0u) {
+                atomicAdd(&s_slot[k], 1u);
+            } else {
+                const uint64_t same = ballot(k == frequent);
+                if (k != frequent) atomicAdd(&s_slot[k], 1u);
+                else if ((same & lanemask_lt()) == 0) atomicAdd(&s_slot[k], (uint32_t)popc64(same));
+            }
+        });
         __syncthreads();
         uint32_t mine = 0;
         for (uint32_t i = tid; i < keys; i += TJ_BUILD_BLOCK) mine += s_slot[i] > 1 ? s_slot[i] + 1 : 0;
@@ -230,9 +245,19 @@ k_table_build(JoinTable t, const uint32_t* dkey, const uint32_t* dval, int64_t n
             }
         }
         __syncthreads();
-        each([&](uint32_t k, uint32_t e) {
-            if (s_slot[k] & TJ_LIST) t.list[(atomicSub(&s_slot[k], 1u) & ~TJ_LIST) - 1] = e;
-            else s_slot[k] = e;
+        each([&](uint32_t k, uint32_t e, uint32_t frequent) {
+            if (!(s_slot[k] & TJ_LIST)) {
+                s_slot[k] = e;
+            } else if (frequent == ~0u || k != frequent) {
+                t.list[(atomicSub(&s_slot[k], 1u) & ~TJ_LIST) - 1] = e;
+            } else {
+                const uint64_t same = ballot(true);
+                const int lead = __ffsll((unsigned long long)same) - 1;
+                uint32_t old = 0;
+                if (lane_id() == lead) old = atomicSub(&s_slot[k], (uint32_t)popc64(same));
+                old = wave_read(old, lead) & ~TJ_LIST;
+                t.list[old - 1 - popc64(same & lanemask_lt())] = e;
+            }
         });
         __syncthreads();
         for (uint32_t i = tid; i < keys; i += TJ_BUILD_BLOCK)

@@ -1,5 +1,5 @@
-"""Dim sides with keys that many rows share, where an atomic per row takes turns on one word: the flags table and the
-pair table against the oracle, at shares from one lane of a wave to all of them, and within the time that the rows'
+"""Dim sides with keys that many rows share, where an atomic per row takes turns on one word: the flags table, the
+pair table and the join table against the oracle, at shares from one lane of a wave to all of them, and within the time that the rows'
 own work takes."""
 import numpy as np
 import pytest
@@ -107,3 +107,48 @@ def test_pairs_time(hip):
     ctx.set_profiling(True)
     hip.fragment_run(*args, key_bits=20, gcap=4)
     assert 0 < _ms(ctx, "fragment_pair_count") < 1.5
+
+
+@pytest.mark.parametrize("shape", ["half", "tenth", "runs", "twice"])
+@pytest.mark.parametrize("sorted_", [False, True])
+@pytest.mark.parametrize("n,m,key_bits", [(20_000, 5_000, 13), (300_000, 70_001, 18), (3_000_000, 90_000, 21)])
+def test_join_table(hip, n, m, key_bits, sorted_, shape):
+    ctx = hip.Context(0)
+    r = np.random.default_rng(n)
+    pk, ck = _keys(shape, m, r), r.integers(0, 5000, m).astype(np.int32)
+    if sorted_:
+        o = np.argsort(pk, kind="stable")
+        pk, ck = pk[o], ck[o]
+    fk = r.integers(4, m, n).astype(np.int32)        # few meet the frequent key
+    fk[:20] = 3
+    fact = {"fk": fk, "date": r.integers(0, 100, n).astype(np.int32), "price": r.integers(1, 10_000, n),
+            "disc": r.integers(0, 11, n)}
+    mid = {"pk": pk, "custkey": ck}
+    want = oracle.fragment_cust(fact, mid, 90, 10, gcap=5000)
+    run = hip.CustFragmentRunner(ctx, hip.to_device(fact), hip.to_device(mid), 90, 10, key_bits=key_bits, cust_bits=13,
+                                 gcap=5000, join_cap=max(n, want["join_rows"]), mid_sorted=sorted_)
+    ctx.set_profiling(True)
+    run.run()
+    assert "probe" in [x for x, _ in ctx.profile_read()]
+    got = run.result()
+    assert ctx.errors() == 0 and got["join_rows"] == want["join_rows"] and got["groups"] == want["groups"]
+    for k in ("key", "sum", "cnt", "top_key", "top_sum", "top_cnt"):
+        assert np.array_equal(got[k], want[k])
+
+
+def test_join_table_time(hip):
+    """1.5M dim rows, half of them on one key: 1.16 ms to build; with an LDS atomic per row 1.94."""
+    import torch
+    ctx = hip.Context(0)
+    n, m = 6_000_000, 1_500_000
+    pk = torch.randperm(m, device="cuda").to(torch.int32)
+    pk[: m // 2] = 0
+    z = lambda t: torch.zeros(n, dtype=t, device="cuda")
+    fact = {"fk": torch.randint(1, m, (n,), dtype=torch.int32, device="cuda"), "date": z(torch.int32),
+            "price": z(torch.int64), "disc": z(torch.int64)}
+    mid = {"pk": pk[torch.randperm(m, device="cuda")].contiguous(), "custkey": torch.zeros(m, dtype=torch.int32, device="cuda")}
+    run = hip.CustFragmentRunner(ctx, fact, mid, 5, 10, key_bits=21, cust_bits=13, gcap=8192)
+    run.run()
+    ctx.set_profiling(True)
+    run.run()
+    assert 0 < _ms(ctx, "table_build") < 1.6
