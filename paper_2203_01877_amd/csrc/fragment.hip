@@ -380,7 +380,7 @@ tqp_status cust_table_launch(tqp_ctx* ctx, const tqp_cust_fragment& f, const tqp
     // date < D and the revenue price * (100 - disc) evaluated as the row is read
     SrcFilterRevenue<VT> fsrc{f.fk, f.date, f.price, f.disc, CMP_LT, f.D, f.n_fact, nullptr};
     if ((st = table_partition(ctx, s, b.tj, fsrc, f.n_fact, "fact_part")) != TQP_OK) return st;
-    if ((st = table_probe(ctx, s, b.tj, fsrc, f.n_fact, "probe", "probe_lists")) != TQP_OK) return st;
+    if ((st = table_probe(ctx, s, b.tj, fsrc, f.n_fact, "probe", "probe_short", "probe_lists")) != TQP_OK) return st;
     // group-by: one block per bucket of custkeys, its first k groups as top-k candidates
     using AV = typename std::conditional<sizeof(VT) == 8, int64_t, uint32_t>::type;
     using Rows = ChunkRows<AV, VT>;

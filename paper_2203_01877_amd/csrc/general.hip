@@ -1015,7 +1015,8 @@ tqp_status table_launch(tqp_ctx* ctx, const tqp_fragment& f, const tqp_fragment_
     }();
     if ((st = table_partition(ctx, s, tj, rows, N, "fragment_part_fact")) != TQP_OK) return st;
     if ((st = side_join(ctx, s)) != TQP_OK) return st;
-    if ((st = table_probe(ctx, s, tj, rows, N, "fragment_probe", "fragment_probe_lists")) != TQP_OK) return st;
+    if ((st = table_probe(ctx, s, tj, rows, N, "fragment_probe", "fragment_probe_short",
+                          "fragment_probe_lists")) != TQP_OK) return st;
     using AV = typename std::conditional<V32, int32_t, int64_t>::type;
     return bucket_groupby<Cfg>(ctx, f, o, b, ChunkRows<AV, V>{tj.grp, o.d_join}, s);
 }

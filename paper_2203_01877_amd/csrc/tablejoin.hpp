@@ -88,7 +88,7 @@ void table_join_reserve(Arena& a, const tqp_ctx* ctx, TableJoin<V>& j, int64_t n
     t.slice_bits = std::min(t.slice_bits, key_bits - t.part_bits);
     t.group_mask = key_mask_for(cb);
     t.slot = a.scratch<uint32_t>(int64_t(1) << key_bits);
-    t.list = a.scratch<uint32_t>(n_dim + n_dim / 2);
+    t.list = a.scratch<uint32_t>(n_dim + n_dim / 2 + 3);      // 3: a list is read with a word behind it
     t.list_n = a.zero<uint32_t>(1);
     if (!dim_sorted) chunks_reserve(a, t.rows, n_dim, nbd, key_bits, t.part_bits);
     const int nb = part_blocks(ctx, n_fact, part_tile<V>());
@@ -288,19 +288,22 @@ inline tqp_status table_build_sorted(tqp_ctx* ctx, hipStream_t s, const JoinTabl
 }
 
 // ------------------------------------------------------------------ probe
-// The table's entry of every row in place of its key: the group key, or
-// PART_NONE where the row has no match or is set aside; place(j) = where item
-// j lies.
-template <class V, class Place>
-__device__ __forceinline__ void probe_rows(const JoinTable& t, const Spill& sp,
-                                           uint32_t (&key)[PartItems<V>::value], const Place& place, bool& wide) {
-    constexpr int ITEMS = PartItems<V>::value;
-    uint32_t any = 0;
+// The table's entry of every row in place of its key (0: no match).
+template <class V>
+__device__ __forceinline__ void probe_entries(const JoinTable& t, uint32_t (&key)[PartItems<V>::value]) {
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
+    for (int j = 0; j < PartItems<V>::value; ++j) {
         const uint32_t e = t.slot[key[j] != PART_NONE ? key[j] : 0u];
         key[j] = key[j] != PART_NONE ? e : 0u;
     }
+}
+// From the entries to the group keys, or PART_NONE where the row has no match
+// or is set aside; place(j) = where item j lies.
+template <class V, class Place>
+__device__ __forceinline__ void probe_rows(const Spill& sp, uint32_t (&key)[PartItems<V>::value], const Place& place,
+                                           bool& wide) {
+    constexpr int ITEMS = PartItems<V>::value;
+    uint32_t any = 0;
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) any |= key[j];
     if (__any((any & (TJ_LIST | TJ_WIDE)) != 0)) {
@@ -329,12 +332,116 @@ __device__ __forceinline__ void probe_rows(const JoinTable& t, const Spill& sp,
     for (int j = 0; j < ITEMS; ++j) key[j] -= 1;      // 0, no match: PART_NONE
 }
 
+// Short lists are expanded by the probe itself: the tile's rows go into the
+// group partitions once per entry, in rounds, instead of through the rows set
+// aside (whose keys, slots, lists and values are read again, by a kernel of one
+// block per CU).  A round costs a tile's barriers whatever it holds, so that
+// lists of up to TJ_SHORT entries take part where a sixteenth of the tile's rows
+// have the longest of them.  Every key on two dim rows, 40M x 10M rows: 1681
+// us, 6M x 1.5M 327, on three 405, on four 424; set aside 2487, 498, 512 and 526, by
+// the sorts 1733, 459, 533 and 627.
+constexpr uint32_t TJ_SHORT = 4;
+constexpr int TJ_SHORT_SHARE = 16;
+
+// The longest lists to expand in place, 0 (none) or 2 to TJ_SHORT, by each
+// wave's first 64 rows.  Called by the whole block.
+template <class V>
+__device__ __forceinline__ uint32_t short_lists(const JoinTable& t, const uint32_t (&key)[PartItems<V>::value],
+                                                uint32_t (&s_len)[PART_BLOCK / WAVE]) {
+    const bool m = (key[0] & TJ_LIST) != 0;
+    const uint32_t len = t.list[m ? key[0] & ~TJ_LIST : 0u];
+    uint32_t n = 0;                    // rows with lists of 2, 3, 4 entries, 10 bits each
+#pragma unroll
+    for (uint32_t q = 0; q <= TJ_SHORT - 2; ++q) n |= (uint32_t)popc64(ballot(m && len == q + 2)) << (10 * q);
+    if (lane_id() == 0) s_len[threadIdx.x / WAVE] = n;
+    __syncthreads();
+    n = 0;
+#pragma unroll
+    for (int w = 0; w < PART_BLOCK / WAVE; ++w) n += s_len[w];
+    uint32_t longest = 0;
+#pragma unroll
+    for (uint32_t q = 0; q <= TJ_SHORT - 2; ++q)
+        if ((n >> (10 * q) & 1023) >= PART_BLOCK / TJ_SHORT_SHARE) longest = q + 2;
+    return __builtin_amdgcn_readfirstlane(longest);
+}
+// Of the tile's lists of at most `longest` entries, entries r and r + 1 (0 past
+// their end), read together: a second read of lists beyond the caches costs
+// more than the registers.  In round 0 the other rows' entries too, in out.
+template <class V>
+__device__ __forceinline__ void round_entries(const JoinTable& t, const uint32_t (&key)[PartItems<V>::value],
+                                              uint32_t r, uint32_t longest, uint32_t (&out)[PartItems<V>::value],
+                                              uint32_t (&next)[PartItems<V>::value]) {
+    constexpr int ITEMS = PartItems<V>::value, FLIGHT = 4;     // read together
+#pragma unroll
+    for (int j0 = 0; j0 < ITEMS; j0 += FLIGHT) {
+        struct List { uint32_t n, e[2]; } x[FLIGHT];           // one read in round 0
+        uint32_t k[FLIGHT];
+#pragma unroll
+        for (int j = 0; j < FLIGHT; ++j) {
+            k[j] = key[j0 + j];
+            asm volatile("" : "+v"(k[j]));             // opaque: no address is kept from round to round
+            const uint32_t at = k[j] & TJ_LIST ? k[j] & ~TJ_LIST : 0u;
+            __builtin_memcpy(&x[j], t.list + at, sizeof(List));
+            if (r) __builtin_memcpy(x[j].e, t.list + (x[j].n > r ? at + 1 + r : at), sizeof x[j].e);
+        }
+#pragma unroll
+        for (int j = 0; j < FLIGHT; ++j) {
+            const bool mine = (k[j] & TJ_LIST) && x[j].n <= longest;
+            out[j0 + j] = mine ? (r < x[j].n ? x[j].e[0] : 0u) : r ? 0u : k[j];
+            next[j0 + j] = mine && r + 1 < x[j].n ? x[j].e[1] : 0u;
+        }
+        asm volatile("" ::: "memory");
+    }
+}
+
+// What a probe kernel is for: any table (its lists set aside); or, from 2^22
+// rows on, one kernel for a table of unique keys and one for a table with lists,
+// of which one returns at once.  In one kernel the registers of the second cost
+// the first 2 to 14%.  A launch for nothing costs 3 to 5 us, 3 to 5% of what 3M
+// rows take, where the lists set aside cost less than the sorts (3M x 750k rows
+// of keys with two dim rows each: 296 and 324 us; 4.1M 359 and 368; 4.3M 302 by
+// the kernel for lists, 382 set aside).
+enum : int { PROBE_ANY = 0, PROBE_UNIQUE = 1, PROBE_LISTS = 2 };
+constexpr int64_t TJ_SHORT_ROWS = int64_t(1) << 22;
+
+// The tile's entries into the group partitions.
+template <int MODE, class V, class Place>
+__device__ __forceinline__ void probe_tile(const JoinTable& t, const Spill& sp, const Chunks<uint16_t, V>& out,
+                                           int parts, uint32_t (&key)[PartItems<V>::value],
+                                           const V (&val)[PartItems<V>::value], const Place& place, bool& wide,
+                                           PartSmem<V>& sm, uint32_t (&s_len)[PART_BLOCK / WAVE]) {
+    probe_entries<V>(t, key);
+    if constexpr (MODE == PROBE_LISTS) {
+        const uint32_t longest = short_lists<V>(t, key, s_len);
+        uint32_t r = 0;
+        uint32_t entry[PartItems<V>::value], next[PartItems<V>::value];
+        do {
+            if (r & 1) {
+#pragma unroll
+                for (int j = 0; j < PartItems<V>::value; ++j) entry[j] = next[j];
+            } else if (longest) {
+                round_entries<V>(t, key, r, longest, entry, next);
+            } else {
+#pragma unroll
+                for (int j = 0; j < PartItems<V>::value; ++j) entry[j] = key[j];
+            }
+            probe_rows<V>(sp, entry, place, wide);
+            part_tile_rows<uint16_t, V, PART_BLOCK>(out, parts, entry, val, sm);
+        } while (++r < longest);
+    } else {
+        probe_rows<V>(sp, key, place, wide);
+        part_tile_rows<uint16_t, V, PART_BLOCK>(out, parts, key, val, sm);
+    }
+}
+
 // The probe over a fact source's rows (a table that fits L2).
-template <class V, class Src>
+template <class V, class Src, int MODE>
 __global__ void __launch_bounds__(PART_BLOCK, PART_WAVES)
 k_probe_cols(Src src, JoinTable t, Spill sp, Chunks<uint16_t, V> out, int parts, uint32_t* flags) {
     constexpr int ITEMS = PartItems<V>::value, TILE = PART_BLOCK * ITEMS;
     __shared__ PartSmem<V> sm;
+    __shared__ uint32_t s_len[PART_BLOCK / WAVE];
+    if (MODE != PROBE_ANY && (*t.list_n != 0) != (MODE == PROBE_LISTS)) return;
     const int w = wave_index(), l = lane_id();
     part_init<uint16_t, V, PART_BLOCK>(sm);
     const int64_t n = src.size();
@@ -347,8 +454,8 @@ k_probe_cols(Src src, JoinTable t, Spill sp, Chunks<uint16_t, V> out, int parts,
         V val[ITEMS];
         const int64_t base = tile * TILE + (int64_t)w * ITEMS * WAVE;
         part_load(src, n, base, key, val, key_mask, bad, bad_key);
-        probe_rows<V>(t, sp, key, [&](int j) { return (uint32_t)(base + j * WAVE + l); }, wide);
-        part_tile_rows<uint16_t, V, PART_BLOCK>(out, parts, key, val, sm);
+        probe_tile<MODE>(t, sp, out, parts, key, val, [&](int j) { return (uint32_t)(base + j * WAVE + l); }, wide, sm,
+                         s_len);
     }
     part_finish<uint16_t, V, PART_BLOCK>(out, parts, sm);
     if (__any(bad_key != 0 || wide) && l == 0) set_flag(flags, FLAG_KEY_RANGE);
@@ -364,7 +471,7 @@ k_probe_cols(Src src, JoinTable t, Spill sp, Chunks<uint16_t, V> out, int parts,
 // costing about 2.3 clocks per lane and CU however it is issued (cached or not,
 // ahead of time or not).  It takes the place of a second pass over the fact
 // rows, the count, the expansion and the pass over its output: 1000 us.
-template <class V>
+template <class V, int MODE>
 __global__ void __launch_bounds__(PART_BLOCK, PART_WAVES)
 k_probe_chunks(Chunks<uint32_t, V> fact, int fact_parts, JoinTable t, Spill sp, Chunks<uint16_t, V> out, int parts,
                uint32_t* flags) {
@@ -373,6 +480,8 @@ k_probe_chunks(Chunks<uint32_t, V> fact, int fact_parts, JoinTable t, Spill sp, 
     static_assert(CPT == probe_chunks<V>(), "the grid's bound");
     __shared__ PartSmem<V> sm;
     __shared__ uint32_t s_item[PART_MAX + 1];         // first item of each partition
+    __shared__ uint32_t s_len[W];
+    const uint32_t lists = MODE == PROBE_ANY ? 0 : *t.list_n;
     const int tid = threadIdx.x, w = wave_index(), l = lane_id();
     part_init<uint16_t, V, PART_BLOCK>(sm);
     {
@@ -383,6 +492,7 @@ k_probe_chunks(Chunks<uint32_t, V> fact, int fact_parts, JoinTable t, Spill sp, 
         if (tid == 0) s_item[fact_parts] = tot;
         __syncthreads();
     }
+    if (MODE != PROBE_ANY && (lists != 0) != (MODE == PROBE_LISTS)) return;
     const uint32_t items = s_item[fact_parts];
     const uint32_t x = blockIdx.x % XCDS, per_xcd = gridDim.x / XCDS;
     const uint32_t i0 = (uint32_t)((uint64_t)items * x / XCDS), i1 = (uint32_t)((uint64_t)items * (x + 1) / XCDS);
@@ -405,9 +515,11 @@ k_probe_chunks(Chunks<uint32_t, V> fact, int fact_parts, JoinTable t, Spill sp, 
 #pragma unroll
         for (int q = 0; q < CPW; ++q) rows[q] = c0 + q < nc ? fact.rows[id[q]] : 0;
     };
+    constexpr bool AHEAD = MODE != PROBE_LISTS;       // (no registers left to read ahead)
     uint32_t it = i0 + blockIdx.x / XCDS;
-    if (it < i1) find(it);
+    if (AHEAD && it < i1) find(it);
     for (; it < i1; it += per_xcd) {
+        if (!AHEAD) find(it);
         int ll = l;
         asm volatile("" : "+v"(ll));                  // opaque, as in part_tile_rows
         uint32_t key[ITEMS];
@@ -424,10 +536,11 @@ k_probe_chunks(Chunks<uint32_t, V> fact, int fact_parts, JoinTable t, Spill sp, 
             if ((uint32_t)((j % PER) * WAVE + ll) >= rows[j / PER]) key[j] = PART_NONE;
         uint32_t at[CPW];
 #pragma unroll
-        for (int q = 0; q < CPW; ++q) at[q] = id[q];
-        if (it + per_xcd < i1) find(it + per_xcd);
-        probe_rows<V>(t, sp, key, [&](int j) { return at[j / PER] * CHUNK + (j % PER) * WAVE + ll; }, wide);
-        part_tile_rows<uint16_t, V, PART_BLOCK>(out, parts, key, val, sm);
+        for (int q = 0; q < CPW; ++q) at[q] = AHEAD ? id[q] : (uint32_t)__builtin_amdgcn_readfirstlane(id[q]);
+        if (AHEAD && it + per_xcd < i1) find(it + per_xcd);
+        probe_tile<MODE>(t, sp, out, parts, key, val,
+                                           [&](int j) { return at[j / PER] * CHUNK + (j % PER) * WAVE + ll; }, wide, sm,
+                                           s_len);
     }
     part_finish<uint16_t, V, PART_BLOCK>(out, parts, sm);
     if (__any(wide) && l == 0) set_flag(flags, FLAG_KEY_RANGE);
@@ -540,21 +653,34 @@ tqp_status table_partition(tqp_ctx* ctx, hipStream_t s, const TableJoin<V>& j, c
 // group partition.
 template <class V, class Src>
 tqp_status table_probe(tqp_ctx* ctx, hipStream_t s, const TableJoin<V>& j, const Src& src, int64_t n_fact,
-                       const char* name, const char* lists_name) {
+                       const char* name, const char* short_name, const char* lists_name) {
     const int parts = 1 << j.grp.part_bits;
     if (n_fact > 0) {
+        auto probe = [&](auto mode, const char* label) -> tqp_status {
+            constexpr int MODE = decltype(mode)::value;
+            if (j.fact_bits)
+                TQP_LAUNCH(ctx, s, label,
+                           (k_probe_chunks<V, MODE><<<(unsigned)j.grp.nblocks, PART_BLOCK, 0, s>>>(
+                               j.fact, 1 << j.fact_bits, j.t, j.spill, j.grp, parts, ctx->d_err)));
+            else
+                TQP_LAUNCH(ctx, s, label,
+                           (k_probe_cols<V, Src, MODE><<<(unsigned)j.grp.nblocks, PART_BLOCK, 0, s>>>(
+                               src, j.t, j.spill, j.grp, parts, ctx->d_err)));
+            return TQP_OK;
+        };
+        tqp_status st;
+        if (n_fact < TJ_SHORT_ROWS) {
+            if ((st = probe(std::integral_constant<int, PROBE_ANY>{}, name)) != TQP_OK) return st;
+        } else {
+            if ((st = probe(std::integral_constant<int, PROBE_UNIQUE>{}, name)) != TQP_OK) return st;
+            if ((st = probe(std::integral_constant<int, PROBE_LISTS>{}, short_name)) != TQP_OK) return st;
+        }
         if (j.fact_bits) {
-            TQP_LAUNCH(ctx, s, name,
-                       (k_probe_chunks<V><<<(unsigned)j.grp.nblocks, PART_BLOCK, 0, s>>>(
-                           j.fact, 1 << j.fact_bits, j.t, j.spill, j.grp, parts, ctx->d_err)));
             using Place = PlaceChunks<V>;
             TQP_LAUNCH(ctx, s, lists_name,
                        (k_probe_lists<V, Place><<<(unsigned)j.dup_blocks, LISTS_BLOCK, 0, s>>>(
                            Place{j.fact.keys, j.fact.vals}, j.t, j.spill, j.grp, parts, ctx->d_err)));
         } else {
-            TQP_LAUNCH(ctx, s, name,
-                       (k_probe_cols<V, Src><<<(unsigned)j.grp.nblocks, PART_BLOCK, 0, s>>>(
-                           src, j.t, j.spill, j.grp, parts, ctx->d_err)));
             using Place = PlaceCols<V, Src>;
             TQP_LAUNCH(ctx, s, lists_name,
                        (k_probe_lists<V, Place><<<(unsigned)j.dup_blocks, LISTS_BLOCK, 0, s>>>(
