@@ -59,7 +59,7 @@ k_filter(FilterPreds fp, int64_t n, const int32_t* carry, int32_t* out_row, int3
          const int64_t* d_n) {
     constexpr int W = BLOCK / WAVE, MASKS = ROUNDS * ITEMS;
     constexpr int64_t TILE = (int64_t)BLOCK * MASKS;
-    __shared__ uint64_t s_mask[W][MASKS];      // survivors of each 64 rows
+    __shared__ uint64_t s_mask[ROUNDS > 1 ? W : 1][MASKS];     // survivors of each 64 rows
     __shared__ int64_t s_wave[W];
     __shared__ int64_t s_base;
     __shared__ uint32_t s_tile;
@@ -78,6 +78,7 @@ k_filter(FilterPreds fp, int64_t n, const int32_t* carry, int32_t* out_row, int3
     }
     const int64_t chunk = tile * TILE + (int64_t)w * MASKS * WAVE;
     int64_t wc = 0;
+    uint64_t mask[ITEMS];                      // of a single round (one in LDS cost a small filter 0.6 us)
 #pragma unroll 1
     for (int r = 0; r < ROUNDS; ++r) {
         const int64_t r0 = chunk + (int64_t)r * ITEMS * WAVE;
@@ -93,7 +94,11 @@ k_filter(FilterPreds fp, int64_t n, const int32_t* carry, int32_t* out_row, int3
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {
             const uint64_t m = ballot(ok[j]);
-            if (l == 0) s_mask[w][r * ITEMS + j] = m;
+            if constexpr (ROUNDS > 1) {
+                if (l == 0) s_mask[w][r * ITEMS + j] = m;
+            } else {
+                mask[j] = m;
+            }
             wc += popc64(m);
         }
     }
@@ -122,7 +127,7 @@ k_filter(FilterPreds fp, int64_t n, const int32_t* carry, int32_t* out_row, int3
         int32_t c[ITEMS];
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {
-            const uint64_t m = s_mask[w][r * ITEMS + j];
+            const uint64_t m = ROUNDS > 1 ? s_mask[ROUNDS > 1 ? w : 0][r * ITEMS + j] : mask[j];
             o[j] = pos + popc64(m & lanemask_lt());
             if (!((m >> l) & 1) || o[j] >= cap) o[j] = -1;
             pos += popc64(m);
