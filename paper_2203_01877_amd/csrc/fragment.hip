@@ -330,16 +330,18 @@ void cust_table_reserve(Arena& a, const tqp_ctx* ctx, const tqp_cust_fragment& f
     b.nbuckets = int64_t(1) << b.tj.grp.part_bits;
     b.sstatus = a.zero<uint64_t>(b.nbuckets);
     b.scounter = a.zero<uint32_t>(1);
-    // top-k candidates: the first k groups of every bucket (at most the groups)
-    b.topk = topk_reserve(a, std::min<int64_t>(o.gcap, b.nbuckets * f.k), f.k);
+    // top-k candidates: the first k groups of every bucket (at most the groups,
+    // and the custkeys there are)
+    const int64_t most = std::min<int64_t>(o.gcap, int64_t(1) << norm_key_bits(f.cust_bits));
+    b.topk = topk_reserve(a, std::min<int64_t>(most, b.nbuckets * f.k), f.k);
 }
 
 // The table where it applies, and where it needs no more scratch than the
 // sorts it replaces (a caller's memory bound that admitted the fragment still
 // does): the spread of its partitions, 0 for the sorts.  Decided by the fragment
 // alone, so that the plan reported is the one run: the top-k's candidates are
-// bounded by gcap on both sides, so no gcap between the two compared makes the
-// table the larger one.
+// bounded by gcap on both sides and by the custkeys on the table's, so no gcap
+// between the two compared or beyond them makes the table the larger one.
 template <class VT>
 int cust_table_fits(const tqp_ctx* ctx, const tqp_cust_fragment& f) {
     if (!table_join_ok(ctx, f.n_fact, f.n_mid, norm_key_bits(f.key_bits), norm_key_bits(f.cust_bits))) return 0;

@@ -58,3 +58,19 @@ def test_general(hip, form):
     assert ("fragment_probe_lists" if form == "keyed" else "fragment_pairs_long") in _names(ctx)
     assert ctx.errors() == hip.DEVERR_CAPACITY and int(out["d_join"]) == pairs
     assert int(out["vals"][1][: int(out["d_ngroups"])].sum()) == cap
+
+
+def test_group_capacity_beyond_the_keys(hip):
+    """A group capacity larger than the custkeys' domain: no more scratch than for the domain, whatever k."""
+    ctx = hip.Context(0)
+    r = np.random.default_rng(3)
+    n, m = 300_000, 90_000
+    fact = hip.to_device({"fk": r.integers(0, m, n).astype(np.int32), "date": r.integers(0, 100, n).astype(np.int32),
+                          "price": r.integers(1, 1000, n), "disc": r.integers(0, 11, n)})
+    mid = hip.to_device({"pk": r.permutation(m).astype(np.int32), "custkey": r.integers(0, 1 << 13, m).astype(np.int32)})
+    runs = [hip.CustFragmentRunner(ctx, fact, mid, 90, 1000, key_bits=17, cust_bits=13, gcap=g << 13) for g in (1, 64)]
+    assert all(x.plan()["mid_passes"] == 1 for x in runs) and runs[0].ws.numel() == runs[1].ws.numel()
+    for x in runs:
+        x.run()
+    a, b = (x.result() for x in runs)
+    assert ctx.errors() == 0 and all(np.array_equal(a[k], b[k]) for k in a)
