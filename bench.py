@@ -85,7 +85,7 @@ def roofline_families(PB):
         "group_pass": ("k_radix_pass<%s, SrcPairs<%s>, %s, 3>" % (cfg, v, v), radix),
         "join_keyval": ("k_join<JoinCfg<256,8,2048>, %s, u32, EmitKeyVal<256,8,%s>, 0>" % (v, v),
                         ("join.hpp", "dev.hpp", "fragment.hpp")),
-        "bucket_agg": ("k_bucket_agg<1024,8192,%s,0,false>" % a, ("segreduce.hpp", "dev.hpp")),
+        "bucket_agg": ("k_bucket_agg<1024,8192,SortedRows<%s>,0,false>" % a, ("segreduce.hpp", "dev.hpp")),
     }
 
 
@@ -101,19 +101,20 @@ def table_bytes(N, n_f, M, J, G, PB, key_bits):
     }
 
 
-def table_families(PB):
-    """As roofline_families, for the join by a key table."""
+def table_families(PB, N):
+    """As roofline_families, for the join by a key table over N fact rows (from 2^22 on the probe is the
+    kernel for tables of unique keys)."""
     v = "u64" if PB == 8 else "u32"
     a = "long" if PB == 8 else "u32"
-    part = ("chunks.hpp", "dev.hpp", "radix.hpp")
-    table = ("tablejoin.hpp", "chunks.hpp", "dev.hpp")
+    part = ("chunks.hpp", "chunkpool.hpp", "dev.hpp", "radix.hpp")
+    table = ("tablejoin.hpp", "chunks.hpp", "chunkpool.hpp", "dev.hpp")
     return {
         "mid_part": ("k_part<u32, u32, SrcKeyCol, 0>", part),
         "table_build": ("k_table_build<false>", table),
         "fact_part": ("k_part<u32, %s, SrcFilterRevenue<%s, false>, 0>" % (v, v), part),
-        "probe": ("k_probe_chunks<%s>" % v, table),
+        "probe": ("k_probe_chunks<%s, %d>" % (v, N >= 1 << 22), table),
         "bucket_agg": ("k_bucket_agg<1024,8192,ChunkRows<%s, %s>,0,false>" % (a, v),
-                       ("segreduce.hpp", "chunks.hpp", "dev.hpp")),
+                       ("segreduce.hpp", "chunks.hpp", "chunkpool.hpp", "dev.hpp")),
     }
 
 
@@ -362,7 +363,7 @@ def main():
     # roofline: the family with the most measured time per step among the big single-stream kernels
     roofline = None
     lbytes = {f: [b] for f, b in family_bytes.items()} if table else launch_bytes(plan, N, n_f, M, J, G, PB)
-    families = table_families(PB) if table else roofline_families(PB)
+    families = table_families(PB, N) if table else roofline_families(PB)
     timed = {f: sum(per[f]) for f in lbytes if f in per}
     if args.digit_bits == 8 and timed:
         fam = max(timed, key=timed.get)

@@ -480,15 +480,17 @@ tqp_status tqp_fragment_cust_plan(tqp_ctx* ctx, const tqp_cust_fragment* f, int*
  * [-2^31, 2^31) on every fact row; when that program reads fact columns
  * only (and the fragment is grouped by one int32 dim column of 16 bits or
  * more) its value is then carried in 32 bits, and a value outside sets
- * TQP_DEVERR_VALUE_RANGE; otherwise the declaration is not used.  The
- * composition is sort-based throughout: both join sides are radix-sorted with
- * their predicates fused into the sort, joined as by tqp_join, the group keys
- * (and, for COUNT(DISTINCT), the distinct values first) radix-sorted with the
- * joined-row index, and each group's run reduced; with one aggregate that has
- * a program (no COUNT(DISTINCT)) and a key of 16 bits or more, the group sort
- * covers the key bits above the last 8 to 13 and each bucket of keys is
- * reduced in LDS.  Over small key domains the join reads a table of the dim
- * side's keys instead of sorting; the results are the same. */
+ * TQP_DEVERR_VALUE_RANGE; otherwise the declaration is not used.  The join
+ * radix-sorts both sides with their predicates fused into the sort and joins
+ * them as by tqp_join; over small key domains (with the context's default
+ * digit width, and where it needs no more scratch) it reads a table of the dim
+ * side's keys instead, with the same results.  The group keys (and, for
+ * COUNT(DISTINCT), the distinct values first) are radix-sorted with the
+ * joined-row index and each group's run reduced; with one aggregate that has a
+ * program (no COUNT(DISTINCT)) and a key of 16 bits or more, the group sort (or
+ * the table's partition) covers the key bits above the last 8 to 13 and each
+ * bucket of keys is reduced in LDS; keys of at most 9 bits are aggregated
+ * without a sort. */
 #define TQP_AGG_COUNT 0
 #define TQP_AGG_SUM 1
 #define TQP_AGG_MIN 2

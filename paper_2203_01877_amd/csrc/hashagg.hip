@@ -312,7 +312,7 @@ __global__ void __launch_bounds__(HA_BLOCK) k_ha_global(HaArgs a) {
 // the end.  A block of 1024 threads per CU, with the next rows in flight and
 // the first slots of all items read at once: bound by the latency of LDS and,
 // with many groups, by the merges' global atomics (30M rows, 1000 groups, every
-// statistic: 411 us with 256 threads per table, 130 so).  A row whose LDS
+// statistic: 411 us with 256 threads per table, 138 so).  A row whose LDS
 // probe fails (a run of HA_LOCAL_PROBE slots of other groups) goes to the
 // global table directly.
 template <bool VAL, bool MINMAX, bool DIST>
