@@ -48,7 +48,10 @@ k_chunks_list(const uint8_t* label, const uint64_t* pool, const uint32_t* dcount
 // At 60k x 15k rows it takes 79 us where the sorts take 152, at 3M x 750k 100
 // against 220, at 60M x 15M 1258 against 1857; with every key on two dim rows 327
 // against 459 at 6M x 1.5M and 1681 against 1733 at 40M x 10M, on eight 660 against
-// 1430.  A digit width set by the caller asks for the sorts.
+// 1430; near the limits (where only a join capacity of several times the fact
+// rows gives the sorts as much scratch) 27M x 6.75M rows over 2^28 keys 1081
+// against 1501, 3.4M x 850k over 2^25 348 against 367.  A digit width set by the
+// caller asks for the sorts.
 bool table_join_ok(const tqp_ctx* ctx, int64_t n_fact, int64_t n_dim, int key_bits, int group_bits) {
     if (ctx->digit_bits != 8) return false;
     if (key_bits > TJ_MAX_KEY_BITS || group_bits > TJ_MAX_GROUP_BITS) return false;
